@@ -27,6 +27,7 @@
 // Each edge's contribution to x_j is stored per (row, slot) and gathered by
 // j over the transposed neighbour and wall-stencil indices: no atomics, a
 // fixed summation order, bitwise repeatable results.
+#include <algorithm>
 #include <type_traits>
 
 #include "device_common.h"
@@ -84,60 +85,242 @@ __global__ void k_adjm_move_prep(const MoveAdjArgs a, int D) {
 }
 
 // ------------------------------------------------------------ S4: lam_a
-// One block per interior particle; for each of its edges the block sums
-// [p_k < 0] sdf(v) w(v) over all velocities (each thread a strided share of
-// the grid, then a fixed-order block sum).
-template <int D, int NC, typename Real>
-__global__ __launch_bounds__(kThreads) void k_adjm_ops(const MoveAdjArgs a, const Real* ops,
-                                                       const Real* f, const double* U,
-                                                       const Real* lam_ft) {
-  constexpr int DD = D * D;
-  __shared__ double sh[4 * DD];
-  const int i = a.plist[blockIdx.x];
+// Sum of v over the 16 lanes of a DPP row, left in every lane of the row
+// (xor 1, xor 2, half mirror, mirror).
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const unsigned long long u = static_cast<unsigned long long>(__double_as_longlong(v));
+  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(u & 0xffffffffu), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(u >> 32), CTRL, 0xF, 0xF, true);
+  return __longlong_as_double(static_cast<long long>(
+      (static_cast<unsigned long long>(static_cast<unsigned>(hi)) << 32) | static_cast<unsigned>(lo)));
+}
+__device__ __forceinline__ double row16_sum(double v) {
+  v = v + dpp_f64<0xB1>(v);
+  v = v + dpp_f64<0x4E>(v);
+  v = v + dpp_f64<0x141>(v);
+  v = v + dpp_f64<0x140>(v);
+  return v;
+}
+// One halving step of a reduce-scatter of two values a, b: with the upper
+// lanes of a and the lower lanes of b exchanged, a + b holds a's pair sums in
+// the lower lanes and b's in the upper ones.  W = 32: halves of the wave,
+// W = 16: neighbouring 16-lane rows.
+template <int W>
+__device__ __forceinline__ double halve_pair(double a, double b) {
+  const unsigned long long ua = static_cast<unsigned long long>(__double_as_longlong(a));
+  const unsigned long long ub = static_cast<unsigned long long>(__double_as_longlong(b));
+  unsigned x[2], y[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const unsigned va = static_cast<unsigned>(ua >> (32 * k)), vb = static_cast<unsigned>(ub >> (32 * k));
+    if constexpr (W == 32) {
+      const auto r = __builtin_amdgcn_permlane32_swap(va, vb, false, false);
+      x[k] = r[0];
+      y[k] = r[1];
+    } else {
+      const auto r = __builtin_amdgcn_permlane16_swap(va, vb, false, false);
+      x[k] = r[0];
+      y[k] = r[1];
+    }
+  }
+  return __longlong_as_double(static_cast<long long>((static_cast<unsigned long long>(x[1]) << 32) | x[0])) +
+         __longlong_as_double(static_cast<long long>((static_cast<unsigned long long>(y[1]) << 32) | y[0]));
+}
+
+// One block per interior particle i; lane L of the block takes groups L,
+// L + lanes, ... of R velocities along the stepping axis (x in 2D; z in 3D,
+// where R.w is constant along it).  A ragged last group of a column overlaps
+// the one before it, with the adjoint taken as zero on the overlap.  The
+// edges of i are taken four at a time: each lane forms its D*D partial sums
+//   sum_r [a_k.w < 0] sdf w = (sum_r sdf w - sum_r sign(a_k.w) sdf w) / 2
+// of every edge, the wave reduces the 4 D*D sums (two halving steps by lane
+// swaps, then the 16-lane rows by DPP moves), and the waves' parts are
+// added in wave order once per kOpsB edges.  i's own rows stay in registers
+// when one group per lane covers the grid.  Bound by FP64 VALU issue and the
+// latency of its row loads at 2-3 waves per SIMD: 6.04 -> 1.95 ms at 25^3 x
+// 14^3 and 0.58 -> 0.16 ms at 100^2 x 24^2 against one block sum of D*D
+// values, with two barriers, per edge and one velocity per thread.
+constexpr int kOpsB = 32;   // edges staged and reduced between two barriers
+constexpr int kOpsWaves = 8;
+
+template <int D, int NC, typename Real, int R>
+__global__ __launch_bounds__(kOpsWaves * 64) void k_adjm_ops(const MoveAdjArgs a, const Real* __restrict__ ops,
+                                                   const Real* __restrict__ f,
+                                                   const double* __restrict__ U,
+                                                   const Real* __restrict__ lam_ft, int groups,
+                                                   double* __restrict__ lam_a) {
+  constexpr int DD = D * D, FA = D == 3 ? 2 : 0, KV = 2;
+  __shared__ double part[kOpsB][kOpsWaves][DD];
+  __shared__ Real rec[kOpsB][DD];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, nw = blockDim.x >> 6;
+  const int i = a.plist[xcd_logical_block(blockIdx.x, gridDim.x)];
   const size_t NVs = a.NV, cs = static_cast<size_t>(a.N) * NVs;
   const int m = min(a.ncnt[i], a.cap);
   const int64_t row = static_cast<int64_t>(i) * a.cap;
-  double Ui[3] = {0.0, 0.0, 0.0};
+  const int nv = a.nv, zs = FA == 0 ? 1 : nv * nv;
+  const uint32_t zsb = static_cast<uint32_t>(zs) * sizeof(Real);
+  const int gc = (nv + R - 1) / R;  // groups of a column
+  const double dv = 2.0 * a.vmax / static_cast<double>(nv - 1);
+  double Ui[D];
 #pragma unroll
   for (int q = 0; q < D; ++q) Ui[q] = U[static_cast<size_t>(q) * a.N + i];
-  for (int e = 0; e < m; ++e) {
-    const int j = a.nidx[row + e];
-    double acc[DD];
+
+  // group g: byte offset of its first velocity, w = v - U there
+  double w0[D];
+  uint32_t qoff = 0;
+  double lam[NC][R], fi[NC][R];
+  auto take = [&](int g) {
+    const bool on = g < groups;
+    const int gg = on ? g : 0;
+    int zg, q, kx[3] = {0, 0, 0};
+    if constexpr (FA == 0) {
+      zg = gg % gc;
+      kx[1] = gg / gc;
+      kx[0] = min(zg * R, nv - R);
+      q = kx[1] * nv + kx[0];
+    } else {
+      const int col = gg % zs;
+      zg = gg / zs;
+      kx[0] = col % nv;
+      kx[1] = col / nv;
+      kx[2] = min(zg * R, nv - R);
+      q = kx[2] * zs + col;
+    }
+    const int skip = on ? zg * R - min(zg * R, nv - R) : R;  // nodes the previous group holds
+    qoff = static_cast<uint32_t>(q) * sizeof(Real);
 #pragma unroll
-    for (int k = 0; k < DD; ++k) acc[k] = 0.0;
-    if (j != i) {
-      double ak[DD];
+    for (int c = 0; c < D; ++c) w0[c] = vnode(kx[c], nv, a.vmax) - Ui[c];
 #pragma unroll
-      for (int k = 0; k < DD; ++k) ak[k] = static_cast<double>(ops[(row + e) * DD + k]);
-      for (int q = threadIdx.x; q < a.NV; q += kThreads) {
-        double v[3], w[D];
-        velocity_of<D>(q, a.nv, a.vmax, v);
+    for (int c = 0; c < NC; ++c) {
+      Real t1[R], t2[R];
+      load_rz<Real, R>(lam_ft + c * cs + static_cast<size_t>(i) * NVs, qoff, zsb, t1);
+      load_rz<Real, R>(f + c * cs + static_cast<size_t>(i) * NVs, qoff, zsb, t2);
 #pragma unroll
-        for (int c = 0; c < D; ++c) w[c] = v[c] - Ui[c];
-        double sdf = 0.0;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          const size_t oi = c * cs + static_cast<size_t>(i) * NVs + q;
-          const size_t oj = c * cs + static_cast<size_t>(j) * NVs + q;
-          sdf = sdf + static_cast<double>(lam_ft[oi]) *
-                          (static_cast<double>(f[oj]) - static_cast<double>(f[oi]));
-        }
-#pragma unroll
-        for (int k = 0; k < D; ++k) {
-          double p = 0.0;
-#pragma unroll
-          for (int c = 0; c < D; ++c) p = p + ak[k * D + c] * w[c];
-          if (p < 0.0) {
-#pragma unroll
-            for (int c = 0; c < D; ++c) acc[k * D + c] = acc[k * D + c] + sdf * w[c];
-          }
-        }
+      for (int r = 0; r < R; ++r) {
+        lam[c][r] = r < skip ? 0.0 : static_cast<double>(t1[r]);
+        fi[c][r] = static_cast<double>(t2[r]);
       }
     }
-    block_sum<DD>(acc, sh);
-    if (threadIdx.x == 0) {
+  };
+  const bool one = groups <= static_cast<int>(blockDim.x);
+  if (one) take(tid);
+
+  // adds 2 sum_r [a_k.w < 0] sdf w of this lane's group at staged edge e,
+  // whose f^n values are fj, to v
+  auto edge = [&](int e, const Real (&fj)[NC][R], double (&v)[DD]) {
+    const Real* o = rec[e];
+    double ak[DD], p[D];
 #pragma unroll
-      for (int k = 0; k < DD; ++k) a.lam_a[(row + e) * DD + k] = -2.0 * a.dt * acc[k];
+    for (int k = 0; k < DD; ++k) ak[k] = static_cast<double>(o[k]);
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+      p[k] = fma(ak[k * D], w0[0], 0.0);  // (never -0: [p < 0] is the sign below)
+#pragma unroll
+      for (int c = 1; c < D; ++c)
+        if (!(D == 3 && k == 2 && c == 2)) p[k] = fma(ak[k * D + c], w0[c], p[k]);
+    }
+    // S: sum sdf, Z: sum sdf (r dv); Sk, Zk: the same with the signs of p_k
+    double S = 0.0, Z = 0.0, Sk[KV], Zk[KV];
+#pragma unroll
+    for (int k = 0; k < KV; ++k) Sk[k] = Zk[k] = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      double sdf = 0.0;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        sdf = fma(lam[c][r], static_cast<double>(fj[c][r]) - fi[c][r], sdf);
+      const double rdv = static_cast<double>(r) * dv, sz = sdf * rdv;
+      S = S + sdf;
+      if (r > 0) Z = Z + sz;
+#pragma unroll
+      for (int k = 0; k < KV; ++k) {
+        const double sg = copysign(1.0, r > 0 ? fma(ak[k * D + FA], rdv, p[k]) : p[k]);
+        Sk[k] = fma(sg, sdf, Sk[k]);
+        if (r > 0) Zk[k] = fma(sg, sz, Zk[k]);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+      double s1, z1;
+      if (k < KV) {
+        s1 = S - Sk[k];
+        z1 = Z - Zk[k];
+      } else {
+        const double h = 1.0 - copysign(1.0, p[k]);
+        s1 = h * S;
+        z1 = h * Z;
+      }
+#pragma unroll
+      for (int c = 0; c < D; ++c) {
+        v[k * D + c] = fma(s1, w0[c], v[k * D + c]);
+        if (c == FA) v[k * D + c] = v[k * D + c] + z1;
+      }
+    }
+  };
+
+  for (int b0 = 0; b0 < m; b0 += kOpsB) {
+    const int bn = min(kOpsB, m - b0), last = bn - 1;
+    // the batch's operators in LDS, its neighbours one per lane of every wave
+    for (int x = tid; x < bn * DD; x += blockDim.x) (&rec[0][0])[x] = ops[(row + b0) * DD + x];
+    const int nb = a.nidx[row + b0 + min(lane, last)];
+    Real fj[2][NC][R];
+    // rows of edges e, e + 1 of the batch at this lane's group
+    auto load = [&](int e) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int j = __builtin_amdgcn_readlane(nb, min(e + s, last));
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          load_rz<Real, R>(f + c * cs + static_cast<size_t>(j) * NVs, qoff, zsb, fj[s][c]);
+      }
+      asm volatile("" ::: "memory");
+    };
+    if (one) load(0);
+    __syncthreads();
+    for (int e0 = 0; e0 < bn; e0 += 4) {
+      // edges e0 + 2h and e0 + 2h + 1, their sums halved over the wave; the
+      // next pair's rows are loaded while these are reduced
+      double half[2][DD];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        double val[2][DD];
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+          for (int k = 0; k < DD; ++k) val[s][k] = 0.0;
+        const int e = e0 + 2 * h;
+        if (one) {
+#pragma unroll
+          for (int s = 0; s < 2; ++s) edge(min(e + s, last), fj[s], val[s]);
+          load(e + 2);
+        } else {
+          for (int g = tid; g < groups; g += blockDim.x) {
+            take(g);
+            load(e);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) edge(min(e + s, last), fj[s], val[s]);
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < DD; ++k) half[h][k] = halve_pair<32>(val[0][k], val[1][k]);
+      }
+      // the two halves share a step over the 16-lane rows: row 0 holds edge
+      // 0, row 1 edge 2, row 2 edge 1, row 3 edge 3
+#pragma unroll
+      for (int k = 0; k < DD; ++k) {
+        const double z = row16_sum(halve_pair<16>(half[0][k], half[1][k]));
+        const int rw = lane >> 4, s = (rw >> 1) | ((rw & 1) << 1);
+        if ((lane & 15) == k && e0 + s < bn) part[e0 + s][wid][k] = z;
+      }
+    }
+    __syncthreads();
+    for (int x = tid; x < bn * DD; x += blockDim.x) {
+      const int e = x / DD, k = x - e * DD;
+      double s = 0.0;
+      for (int w = 0; w < nw; ++w) s = s + part[e][w][k];
+      // (the self edge has zero operators and takes no part)
+      lam_a[(row + b0) * DD + x] = a.nidx[row + b0 + e] == i ? 0.0 : -a.dt * s;
     }
   }
 }
@@ -672,29 +855,63 @@ hipError_t launch_adjoint_wallrow(const Ctx& c) {
   return hipGetLastError();
 }
 
-template <typename Real>
+// R velocities per lane: of 2..8 in 3D, 2..4 in 2D (at most nv) the one with
+// the least work per particle, waves x (R + the per-edge set-up and
+// reduction, worth about 5 velocities in 3D and 3 in 2D), and as many waves
+// as one group per lane takes, at most 8.  Measured per rollout gradient:
+// 25^3 x 14^3, 2 steps, 19.0 ms at R = 7 against 21.4 (5) and 22.2 (4);
+// 100^2 x 24^2, 5 steps, 6.12 ms at R = 3 against 6.62 (2) and 6.32 (4).
+template <int D, int NC, typename Real, int R>
+static void launch_ops_r(const Ctx& c, const MoveAdjArgs& a, const Real* ops, const Real* f,
+                         const double* U_n, const Real* lft) {
+  const int gc = (c.cfg.nv + R - 1) / R, groups = c.NV / c.cfg.nv * gc;
+  const int nt = std::min(kOpsWaves * 64, (groups + 63) / 64 * 64);
+  hipLaunchKernelGGL((k_adjm_ops<D, NC, Real, R>), dim3(c.Ni), dim3(nt), 0, c.stream, a, ops, f,
+                     U_n, lft, groups, a.lam_a);
+}
+
+template <int D, int NC, typename Real>
 static void launch_ops_t(const Ctx& c, const MoveAdjArgs& a, const void* f_n, const double* U_n) {
   const Real* ops = std::is_same<Real, double>::value
                         ? reinterpret_cast<const Real*>(c.d.ops64)
                         : reinterpret_cast<const Real*>(c.d.ops32);
   const Real* f = static_cast<const Real*>(f_n);
   const Real* lft = static_cast<const Real*>(c.adj.lam_ft);
-  if (c.D == 2)
-    hipLaunchKernelGGL((k_adjm_ops<2, 2, Real>), dim3(c.Ni), dim3(kThreads), 0, c.stream, a, ops,
-                       f, U_n, lft);
-  else
-    hipLaunchKernelGGL((k_adjm_ops<3, 1, Real>), dim3(c.Ni), dim3(kThreads), 0, c.stream, a, ops,
-                       f, U_n, lft);
+  int best = 2;
+  int64_t cost = INT64_MAX;
+  for (int R = 2; R <= 8 && R <= c.cfg.nv; ++R) {
+    if (D == 2 && R > 4) break;
+    const int64_t groups = static_cast<int64_t>(c.NV / c.cfg.nv) * ((c.cfg.nv + R - 1) / R);
+    const int64_t w = (groups + 63) / 64 * (R + (D == 3 ? 5 : 3));
+    if (w < cost) {
+      cost = w;
+      best = R;
+    }
+  }
+  switch (best) {
+    case 2: launch_ops_r<D, NC, Real, 2>(c, a, ops, f, U_n, lft); break;
+    case 3: launch_ops_r<D, NC, Real, 3>(c, a, ops, f, U_n, lft); break;
+    case 4: launch_ops_r<D, NC, Real, 4>(c, a, ops, f, U_n, lft); break;
+    default:
+      if constexpr (D == 3) {
+        if (best == 6) launch_ops_r<D, NC, Real, 6>(c, a, ops, f, U_n, lft);
+        else if (best == 5) launch_ops_r<D, NC, Real, 5>(c, a, ops, f, U_n, lft);
+        else if (best == 7) launch_ops_r<D, NC, Real, 7>(c, a, ops, f, U_n, lft);
+        else launch_ops_r<D, NC, Real, 8>(c, a, ops, f, U_n, lft);
+      }
+  }
 }
 
 hipError_t launch_adjoint_move_geometry(const Ctx& c, const void* f_n, const double* U_n,
                                         const double* x, double* lam_x) {
   const MoveAdjArgs a = move_args(c, x, nullptr, nullptr, lam_x);
   if (c.Ni) {
-    if (c.cfg.precision == BGK_FP64)
-      launch_ops_t<double>(c, a, f_n, U_n);
-    else
-      launch_ops_t<float>(c, a, f_n, U_n);
+    const bool f64 = c.cfg.precision == BGK_FP64;
+    if (c.D == 2) {
+      if (f64) launch_ops_t<2, 2, double>(c, a, f_n, U_n); else launch_ops_t<2, 2, float>(c, a, f_n, U_n);
+    } else {
+      if (f64) launch_ops_t<3, 1, double>(c, a, f_n, U_n); else launch_ops_t<3, 1, float>(c, a, f_n, U_n);
+    }
     const dim3 g((c.Ni + 63) / 64), b(64);
     if (c.D == 2)
       hipLaunchKernelGGL(k_adjm_geom<2>, g, b, 0, c.stream, a);

@@ -9,7 +9,7 @@
 // Layout of the work: a block owns one patch; thread tid handles R
 // velocities q = q0 + r zs (r < R, R divides nv) that differ only in one
 // velocity component, the stepping axis: each projection a_k.(v - U) is
-// formed once and then advanced by a constant per r (one add).  In 2D the
+// formed once per RB of them and then advanced by a constant per r (one add).  In 2D the
 // stepping axis is the fastest one, x (zs = 1: every row access of a thread
 // is one contiguous R-element vector load or store).  In 3D it is z (zs =
 // nv^2): the third frame vector has no z component, so its projection is
@@ -38,6 +38,8 @@
 // (large 3D grids in FP64) the velocity range is split into tiles over
 // several blocks; the kernel then writes f-tilde and the separate
 // relaxation kernel finishes the step.
+#include <type_traits>
+
 #include "device_common.h"
 
 namespace bgk {
@@ -183,7 +185,7 @@ constexpr int pow2_at_least(int n) { return n <= 1 ? 1 : 2 * pow2_at_least((n + 
 // f-tilde of every tile but the last waits in LDS (thread-private slots, no
 // barrier), so the moments and the relaxation run in the same block and
 // f-tilde never goes to HBM.
-template <int D, int NC, int MODE, int R, bool FUSE, int TP, bool INLDS>
+template <int D, int NC, int MODE, int R, int RB, bool FUSE, int TP, bool INLDS>
 __global__ __launch_bounds__(1024) void k_fused(const FusedArgs a) {
   using Real = typename FPrec<MODE>::real;
   constexpr int DD = D * D;
@@ -316,6 +318,11 @@ __global__ __launch_bounds__(1024) void k_fused(const FusedArgs a) {
 #pragma unroll
   for (int k = 0; k < D; ++k) v0[k] = static_cast<Real>(vtab[kq[k]]);
   if constexpr (LEAN) v0[FA] = static_cast<Real>(kq[FA]) - static_cast<Real>(0.5 * (a.nv - 1));
+  // stepping-axis velocity r of the lane, where the projections are formed anew
+  Real vsb[R / RB];
+#pragma unroll
+  for (int i = 1; i < R / RB; ++i) vsb[i] = static_cast<Real>(vtab[kq[FA] + i * RB]);
+  auto vs = [&](int r) { return vsb[r / RB]; };
 
   auto load_self = [&](int t, int c, Real (&o)[R]) {
     Real tmp[R];
@@ -461,6 +468,18 @@ __global__ __launch_bounds__(1024) void k_fused(const FusedArgs a) {
             if constexpr (V16) return rv[k];
             return rec[k];
           };
+          // projection k at stepping-axis velocity vs, the terms in axis order
+          Real pre[D], as[D];  // (3D: the terms before the stepping axis, shared)
+          auto at = [&](int k, Real vs) {
+            if constexpr (FA == 0) {
+              Real s1 = fma_t(as[k], vs, pre[k]);
+#pragma unroll
+              for (int m = 1; m < D; ++m) s1 = fma_t(rc(ia(k, m)), v0[m], s1);
+              return s1;
+            } else {
+              return (RZ0 && k == D - 1) ? pre[k] : fma_t(as[k], vs, pre[k]);
+            }
+          };
           if constexpr (R >= 8) {
             // many velocities per thread: read the per-edge rows one at a
             // time, so that their registers are not all live at once
@@ -468,9 +487,10 @@ __global__ __launch_bounds__(1024) void k_fused(const FusedArgs a) {
             for (int k = 0; k < D; ++k) {
               Real s1 = -rec[ib(k)];
 #pragma unroll
-              for (int m = 0; m < D; ++m)
-                if (!(RZ0 && k == D - 1 && m == D - 1)) s1 = fma_t(rec[ia(k, m)], v0[m], s1);
-              p[k] = s1;
+              for (int m = 0; m < FA; ++m) s1 = fma_t(rec[ia(k, m)], v0[m], s1);
+              pre[k] = s1;
+              as[k] = rec[ia(k, FA)];
+              p[k] = at(k, v0[FA]);
               asm volatile("" ::: "memory");
             }
           } else {
@@ -485,21 +505,14 @@ __global__ __launch_bounds__(1024) void k_fused(const FusedArgs a) {
                 for (int w = 0; w < W; ++w) rv[i * W + w] = x[w];
               }
             }
-            Real av[DD], bk[D];
-#pragma unroll
-            for (int k = 0; k < D; ++k)
-#pragma unroll
-              for (int m = 0; m < D; ++m)
-                av[k * D + m] = (RZ0 && k == D - 1 && m == D - 1) ? Real(0) : rc(ia(k, m));
-#pragma unroll
-            for (int k = 0; k < D; ++k) bk[k] = rc(ib(k));
 #pragma unroll
             for (int k = 0; k < D; ++k) {
-              Real s1 = -bk[k];
+              Real s1 = -rc(ib(k));
 #pragma unroll
-              for (int m = 0; m < D; ++m)
-                if (!(RZ0 && k == D - 1 && m == D - 1)) s1 = fma_t(av[k * D + m], v0[m], s1);
-              p[k] = s1;
+              for (int m = 0; m < FA; ++m) s1 = fma_t(rc(ia(k, m)), v0[m], s1);
+              pre[k] = s1;
+              as[k] = rc(ia(k, FA));
+              p[k] = at(k, v0[FA]);
             }
           }
 #pragma unroll
@@ -507,12 +520,16 @@ __global__ __launch_bounds__(1024) void k_fused(const FusedArgs a) {
           // the projections past KV are constant along the lane's velocities:
           // their terms are formed once (GW: folded into g.w)
           Real gw = Real(0), ig = Real(0), cfix = Real(0);
+          auto gw_of = [&]() {
+            Real g = p[0];
+#pragma unroll
+            for (int k = 1; k < D; ++k) g = g + p[k];
+#pragma unroll
+            for (int k = KV; k < D; ++k) g = g - abs_t(p[k]);
+            return g;
+          };
           if constexpr (GW) {
-            gw = p[0];
-#pragma unroll
-            for (int k = 1; k < D; ++k) gw = gw + p[k];
-#pragma unroll
-            for (int k = KV; k < D; ++k) gw = gw - abs_t(p[k]);
+            gw = gw_of();
             ig = rc(IG);
           } else if constexpr (KV < D) {
             cfix = min_t(p[KV], Real(0));
@@ -521,7 +538,11 @@ __global__ __launch_bounds__(1024) void k_fused(const FusedArgs a) {
           }
 #pragma unroll
           for (int r = 0; r < R; ++r) {
-            if (r > 0) {
+            if (r > 0 && r % RB == 0) {
+#pragma unroll
+              for (int k = 0; k < KV; ++k) p[k] = at(k, vs(r));
+              if constexpr (GW) gw = gw_of();
+            } else if (r > 0) {
 #pragma unroll
               for (int k = 0; k < KV; ++k) p[k] = p[k] + ik[k];
               if constexpr (GW) gw = gw + ig;
@@ -559,7 +580,7 @@ __global__ __launch_bounds__(1024) void k_fused(const FusedArgs a) {
       // velocities per lane: the four-row ring fits the registers.  In 3D,
       // with one component, the doubled per-edge set-up costs more than the
       // packed products save.)
-      auto setup = [&](int uu, int t, bool on, Real (&p)[D], Real (&ik)[D]) {
+      auto setup = [&](int uu, int t, bool on, Real vf, Real (&p)[D], Real (&ik)[D]) {
 #pragma unroll
         for (int k = 0; k < D; ++k) {
           p[k] = Real(0);
@@ -571,7 +592,7 @@ __global__ __launch_bounds__(1024) void k_fused(const FusedArgs a) {
         for (int k = 0; k < D; ++k) {
           Real s1 = -rec[ib(k)];
 #pragma unroll
-          for (int m = 0; m < D; ++m) s1 = fma_t(rec[ia(k, m)], v0[m], s1);
+          for (int m = 0; m < D; ++m) s1 = fma_t(rec[ia(k, m)], m == FA ? vf : v0[m], s1);
           p[k] = s1;
           ik[k] = rec[ii(k)];
         }
@@ -593,11 +614,14 @@ __global__ __launch_bounds__(1024) void k_fused(const FusedArgs a) {
           const bool ta = (ma >> t) & 1u, tb = (mb >> t) & 1u;
           if (!(ta || tb)) continue;
           Real pa[D], ia[D], pb[D], ib[D];
-          setup(u, t, ta, pa, ia);
-          setup(u + 1, t, tb, pb, ib);
+          setup(u, t, ta, v0[FA], pa, ia);
+          setup(u + 1, t, tb, v0[FA], pb, ib);
 #pragma unroll
           for (int r = 0; r < R; ++r) {
-            if (r > 0) {
+            if (r > 0 && r % RB == 0) {
+              setup(u, t, ta, vs(r), pa, ia);
+              setup(u + 1, t, tb, vs(r), pb, ib);
+            } else if (r > 0) {
 #pragma unroll
               for (int k = 0; k < D; ++k) {
                 pa[k] = pa[k] + ia[k];
@@ -890,16 +914,43 @@ __global__ __launch_bounds__(1024) void k_fused(const FusedArgs a) {
 }
 
 // Launch plan: R velocities per thread along the stepping axis (R divides
-// nv, so a thread's R velocities share every other component), at most
-// Rmax for the precision and model (the per-thread accumulators are
-// tp * R * (n_c + 1) values), and the fewest velocity tiles of at most
-// 1024 threads (2D: fewer, see lanes_max).  One tile runs the fused
-// relaxation.  Several FP64 tiles whose f-tilde (all but the last tile)
-// fits the LDS next to the kernel's own tables are walked in turn by one
-// block per patch (inlds), which then relaxes them; otherwise each tile is
-// a block that writes f-tilde, and the separate relaxation kernel finishes.
+// nv, so a thread's R velocities share every other component), at most what
+// the registers of the precision and model allow (the per-thread
+// accumulators are tp * R * (n_c + 1) values).  The projections are formed
+// anew every RB of them (RB divides R) and advanced in between.
+//
+// RB: the smallest width that one tile of at most 1024 lanes fits (2D: 256, or
+// 512 for FP64 with 4-particle patches), which spreads a small cloud over the
+// most waves, or else the largest and the fewest velocity tiles of at most
+// 1024 threads.  In FP32 and BF16 modes RB fixes the rounding of the
+// projections, so it follows from the grid alone, and R only widens the lane;
+// FP64 takes RB = R.
+//
+// Clouds with patches to spare are bound by throughput: an edge's record
+// reads and set-up are shared by R velocities, and blocks small enough for
+// two or more per CU overlap one block's phases (staging, sums, relaxation)
+// with another's walk.
+//  3D from 512 patches: the largest R whose block has at least 128 lanes (256
+//    below 1024 patches and in BF16 mode) and at most 512, or the first that
+//    needs one tile where RB needs several.  Fused kernel, R against RB, us:
+//    32^3 x 16^3 FP32 R 8 1093, 4 1397, BF16 863 and 1171; 26^3 FP32: 8^3 R
+//    4 122, 1 180; 10^3 R 5 226, 1 343; 12^3 R 4 359, 2 525 (R 6 432); 18^3 R
+//    6 974, 2 in three tiles 1331; FP64: 8^3 R 4 172, 1 289; 10^3 R 2 373, 1
+//    636; 12^3 R 4 524, 2 713.  At 250 patches the order turns (8^3 FP32 R 4
+//    40, 1 32).
+//  2D from 2048 patches (FP64: 1024; not BF16, whose two-row pairs gain
+//    nothing: 150^2 x 12^2 102 against 83): the least waves x (R + 3.2), an
+//    edge's set-up being worth about 3.2 velocities; ragged last waves count
+//    in full.  500^2 x 20^2 FP32 R 4 1183, 2 1377; 300^2 x 16^2 R 4 209, 1
+//    286; 150^2 x 14^2 FP64 R 2 84, 1 114.
+//
+// One tile runs the fused relaxation.  Several FP64 tiles whose f-tilde (all
+// but the last tile) fits the LDS next to the kernel's own tables are walked
+// in turn by one block per patch (inlds), which then relaxes them; otherwise
+// each tile is a block that writes f-tilde, and the separate relaxation
+// kernel finishes.
 struct FusedPlan {
-  int R = 0, tiles = 0, bte = 0;
+  int R = 0, RB = 0, tiles = 0, bte = 0;
   bool inlds = false;
   size_t lds = 0;   // dynamic LDS bytes of the inlds variant
 };
@@ -910,54 +961,110 @@ struct FusedPlan {
 constexpr size_t kLdsBytes = 160 * 1024;
 constexpr size_t kFusedStaticLds = 34 * 1024;
 
-// Instantiated (patch size, R) pairs per model and precision, within the
+// Instantiated (patch size, R, RB) per model and precision, within the
 // register budget.
-template <int D, int MODE, int TP, int R>
+template <int D, int MODE, int TP, int R, int RB>
 constexpr bool fused_instance() {
-  if (MODE == BGK_FP64) return (R == 1 || R == 2 || R == 4) && !(D == 2 && TP == 4 && R == 4);
-  if (D == 2) return TP == 4 && (R == 1 || R == 2 || R == 4 || R == 5);
-  return TP == 4 && (R == 1 || R == 2 || R == 4 || R == 5 || R == 8 || R == 10);
+  if (MODE == BGK_FP64)
+    return R == RB &&
+           (R == 1 || R == 2 || (D == 3 && R == 3) || (R == 4 && !(D == 2 && TP == 4)));
+  if (TP != 4) return false;
+  if (D == 2)
+    return (R == RB && (R == 1 || R == 2 || R == 4)) ||
+           (MODE == BGK_FP32 && ((RB == 1 && (R == 2 || R == 4)) || (RB == 2 && R == 4)));
+  return (R == RB && (R == 1 || R == 2 || R == 4 || R == 5 || R == 8 || R == 10)) ||
+         (RB == 1 && (R == 2 || R == 4 || R == 5)) || (RB == 2 && (R == 4 || R == 6)) ||
+         (RB == 4 && R == 8);
+}
+
+// f(integral_constant R, integral_constant RB) for the instantiated pair.
+template <int D, int MODE, int TP, typename F>
+static bool with_fused_r(int R, int RB, F&& f) {
+  bool done = false;
+  auto one = [&](auto r, auto rb) {
+    if constexpr (fused_instance<D, MODE, TP, decltype(r)::value, decltype(rb)::value>()) {
+      if (R == decltype(r)::value && RB == decltype(rb)::value) {
+        f(r, rb);
+        done = true;
+      }
+    }
+  };
+  auto row = [&](auto r) {
+    one(r, std::integral_constant<int, 1>{});
+    if constexpr (decltype(r)::value > 1) one(r, std::integral_constant<int, 2>{});
+    if constexpr (decltype(r)::value > 2) one(r, std::integral_constant<int, 4>{});
+    if constexpr (decltype(r)::value != 1 && decltype(r)::value != 2 && decltype(r)::value != 4)
+      one(r, r);
+  };
+  row(std::integral_constant<int, 1>{});
+  row(std::integral_constant<int, 2>{});
+  row(std::integral_constant<int, 3>{});
+  row(std::integral_constant<int, 4>{});
+  row(std::integral_constant<int, 5>{});
+  row(std::integral_constant<int, 6>{});
+  row(std::integral_constant<int, 8>{});
+  row(std::integral_constant<int, 10>{});
+  return done;
+}
+
+static bool fused_pair(const Ctx& c, int R, int RB) {
+  auto none = [](auto, auto) {};
+  if (c.D == 2) {
+    if (c.cfg.precision == BGK_FP64)
+      return c.tp == 2 ? with_fused_r<2, BGK_FP64, 2>(R, RB, none)
+                       : with_fused_r<2, BGK_FP64, 4>(R, RB, none);
+    return c.cfg.precision == BGK_FP32 ? with_fused_r<2, BGK_FP32, 4>(R, RB, none)
+                                       : with_fused_r<2, BGK_BF16, 4>(R, RB, none);
+  }
+  if (c.cfg.precision == BGK_FP64) return with_fused_r<3, BGK_FP64, 4>(R, RB, none);
+  return with_fused_r<3, BGK_FP32, 4>(R, RB, none);
 }
 
 static FusedPlan plan_fused(const Ctx& c) {
   const int D = c.D, nv = c.cfg.nv, NV = c.NV;
   const bool f64 = c.cfg.precision == BGK_FP64;
-  // instantiated R, ascending
-  static const int r64[] = {1, 2, 4};
-  static const int r2d[] = {1, 2, 4, 5};
-  static const int r3d[] = {1, 2, 4, 5, 8, 10};
   const bool wide = D == 2 && f64 && c.tp == 4;  // FP64 2D with 4-particle patches
-  const int rmax = D == 2 ? (wide ? 2 : 4) : (f64 ? 4 : 10);
-  const int* cand = f64 ? r64 : (D == 2 ? r2d : r3d);
-  const int ncand = f64 ? 3 : (D == 2 ? 4 : 6);
-  // 2D: at most 256 lanes, i.e. 4 velocities per lane at 32^2 (fewer,
-  // wider row loads and one projection set-up per 4 velocities), or 512
-  // lanes of 2 velocities for FP64 with 4-particle patches
+  constexpr int kRmax = 10;
   const int lanes_max = D == 2 ? (wide ? 512 : 256) : 1024;
   FusedPlan p;
-  // one tile: the smallest admissible R that fits
-  for (int i = 0; i < ncand; ++i) {
-    const int R = cand[i];
-    if (R > rmax || nv % R || NV / R > lanes_max) continue;
-    p.R = R;
-    p.tiles = 1;
-    p.bte = NV / R;
-    return p;
-  }
-  // several tiles: the largest admissible R
-  for (int i = ncand - 1; i >= 0; --i) {
-    const int R = cand[i];
-    if (R > rmax || nv % R) continue;
-    const int lanes = NV / R;
-    p.R = R;
-    p.tiles = (lanes + 1023) / 1024;
-    p.bte = (lanes + p.tiles - 1) / p.tiles;
-    if (f64) {
-      const size_t nc = D == 2 ? 2 : 1;
-      p.lds = static_cast<size_t>(p.tiles - 1) * c.tp * R * nc * p.bte * sizeof(double);
-      p.inlds = p.lds + kFusedStaticLds <= kLdsBytes;
+  // R = RB: one tile of the smallest R that fits, or else several of the largest
+  for (int R = 1; R <= kRmax && p.R == 0; ++R)
+    if (nv % R == 0 && fused_pair(c, R, R) && NV / R <= lanes_max) p.R = R;
+  for (int R = kRmax; R >= 1 && p.R == 0; --R)
+    if (nv % R == 0 && fused_pair(c, R, R)) p.R = R;
+  if (p.R == 0) return p;
+  p.RB = p.R;
+  // clouds with patches to spare
+  const bool bf = c.cfg.precision == BGK_BF16;
+  const int lanes_min = c.npatch >= 1024 && !bf ? 128 : 256;
+  int best = 0;
+  double cost = 0.0;
+  for (int R = 1; R <= kRmax; ++R) {
+    const int RB = f64 ? R : p.RB, lanes = NV / R;
+    if (nv % R || R % RB || !fused_pair(c, R, RB)) continue;
+    if (D == 3 && c.npatch >= 512) {
+      // (R = 6 only where nothing else leaves one tile)
+      if (lanes <= 512 && R != 6 ? lanes >= lanes_min : lanes <= 1024 && best == 0 && NV / p.R > 1024)
+        best = R;
+    } else if (D == 2 && c.npatch >= (f64 ? 1024 : 2048)) {
+      const double w = (lanes + 63) / 64 * (R + 3.2);
+      if (lanes <= 1024 && (best == 0 || w < cost)) {
+        best = R;
+        cost = w;
+      }
     }
-    return p;
+  }
+  if (best) {
+    p.R = best;
+    if (f64) p.RB = best;
+  }
+  const int lanes = NV / p.R;
+  p.tiles = (lanes + 1023) / 1024;
+  p.bte = (lanes + p.tiles - 1) / p.tiles;
+  if (f64 && p.tiles > 1) {
+    const size_t nc = D == 2 ? 2 : 1;
+    p.lds = static_cast<size_t>(p.tiles - 1) * c.tp * p.R * nc * p.bte * sizeof(double);
+    p.inlds = p.lds + kFusedStaticLds <= kLdsBytes;
   }
   return p;
 }
@@ -975,41 +1082,25 @@ static hipError_t launch_fused_t(const Ctx& c, FusedArgs a, const FusedPlan& p) 
   const size_t lds = inlds ? p.lds : 0;
   // (the dynamic LDS size is set on the kernel before the launch: gfx950
   // gives one workgroup up to 160 KB)
-#define BGK_LAUNCH_FUSED(RR, IL)                                                          \
-  do {                                                                                    \
-    auto kf = k_fused<D, NC, MODE, RR, FUSE, TP, IL>;                                     \
-    if (lds) {                                                                            \
-      const hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(kf),        \
-          hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));             \
-      if (ea != hipSuccess) return ea;                                                    \
-    }                                                                                     \
-    hipLaunchKernelGGL(kf, g, b, lds, c.stream, a);                                       \
-  } while (0)
-  switch (p.R) {
-#define BGK_R_CASE(RR)                                                                    \
-  case RR:                                                                                \
-    if constexpr (fused_instance<D, MODE, TP, RR>()) {                                    \
-      if constexpr (FUSE && MODE == BGK_FP64) {                                           \
-        if (inlds) BGK_LAUNCH_FUSED(RR, true);                                            \
-        else BGK_LAUNCH_FUSED(RR, false);                                                 \
-      } else {                                                                            \
-        BGK_LAUNCH_FUSED(RR, false);                                                      \
-      }                                                                                   \
-    } else {                                                                              \
-      return hipErrorInvalidValue;                                                        \
-    }                                                                                     \
-    break;
-    BGK_R_CASE(1)
-    BGK_R_CASE(2)
-    BGK_R_CASE(4)
-    BGK_R_CASE(5)
-    BGK_R_CASE(8)
-    BGK_R_CASE(10)
-#undef BGK_R_CASE
-#undef BGK_LAUNCH_FUSED
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  hipError_t err = hipSuccess;
+  auto launch = [&](auto kf) {
+    if (lds)
+      err = hipFuncSetAttribute(reinterpret_cast<const void*>(kf),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+    if (err == hipSuccess) hipLaunchKernelGGL(kf, g, b, lds, c.stream, a);
+  };
+  const bool known = with_fused_r<D, MODE, TP>(p.R, p.RB, [&](auto r, auto rb) {
+    constexpr int R = decltype(r)::value, RB = decltype(rb)::value;
+    if constexpr (FUSE && MODE == BGK_FP64) {
+      if (inlds) {
+        launch(k_fused<D, NC, MODE, R, RB, FUSE, TP, true>);
+        return;
+      }
+    }
+    launch(k_fused<D, NC, MODE, R, RB, FUSE, TP, false>);
+  });
+  if (!known) return hipErrorInvalidValue;
+  return err == hipSuccess ? hipGetLastError() : err;
 }
 
 template <bool FUSE>

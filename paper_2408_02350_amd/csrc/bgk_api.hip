@@ -142,6 +142,10 @@ size_t workspace_layout(const bgk_config& cfg, char* base, Dev* d, Adj* adj, Pm*
   t.uj = reinterpret_cast<int32_t*>(take((N + 3) * cap * 4));
   t.ue = reinterpret_cast<uint32_t*>(take((N + 3) * cap * 4));
   t.jpart = reinterpret_cast<double*>(take(N * 8));
+  // block sums of the scans (cell keys, particles, lattice nodes)
+  int64_t scan_n = std::max(2 * ncell, N);
+  if (cfg.flags & BGK_FLAG_PARTICLES) scan_n = std::max(scan_n, ipow(lattice_nodes(cfg), cfg.dim));
+  t.scansum = reinterpret_cast<int32_t*>(take((scan_n / kScanChunk + 1) * 4));
   t.scheck = reinterpret_cast<double*>(take((N + 1) * kCheckTerms * 8));
   const int64_t npw = wall_patches_max(N, cfg.dim);
   t.wpl = reinterpret_cast<int32_t*>(take(npw * kWallPatch * 4));

@@ -31,6 +31,7 @@ inline int choose_patch(int dim, int precision, int NV, int Ni) {
   const int lanes = NV / 2;
   return (lanes % 64 == 0 && lanes <= 512 && (Ni + 3) / 4 >= 1024) ? 4 : 2;
 }
+constexpr int kScanChunk = 8192;  // entries one block scans
 constexpr int kThreads = 256;   // threads per block of the per-particle kernels
 
 // bit of the device error word for each status code
@@ -68,6 +69,7 @@ struct Dev {
   int32_t* wuj;          // [npw][kWallPatch*cap] union of the patch's wall rows
   uint32_t* wue;         // [npw][kWallPatch*cap] packed 8-bit slot in each wall row
   double* jpart;         // [N]   per-particle terms of the objective
+  int32_t* scansum;      // [scan_blocks] block sums of the long scans
   double* scheck;        // [N][kCheckTerms] per-particle terms of bgk_state_check, then its sums
 };
 
@@ -165,9 +167,8 @@ size_t workspace_layout(const bgk_config& cfg, char* base, Dev* d, Adj* adj, Pm*
 // ---- launchers (enqueue on c.stream; return hipError_t of the launch) ----
 hipError_t launch_fill_i32(hipStream_t s, int32_t* p, int64_t n, int32_t v);
 hipError_t launch_fill_f64(hipStream_t s, double* p, int64_t n, double v);
-hipError_t launch_copy_i32(hipStream_t s, const int32_t* src, int32_t* dst, int64_t n);
 hipError_t launch_max_i32(hipStream_t s, const int32_t* a, int n, int32_t* out);
-hipError_t launch_scan(hipStream_t s, int32_t* a, int n);  // exclusive, a[n] = total
+hipError_t launch_scan(const Ctx& c, int32_t* a, int n, int32_t* copy = nullptr);  // exclusive, a[n] = total
 hipError_t launch_scatter_wall_rows(const Ctx& c, int32_t* cnt_out, int32_t* idx_out,
                                     double* c0_out, double* hb_out);
 

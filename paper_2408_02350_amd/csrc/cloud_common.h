@@ -47,6 +47,15 @@ __device__ __forceinline__ int cell_key(const int* cc, int nca) {
 // patch or wall particle; lanes work on candidates / neighbours in parallel.
 constexpr int kWave = 64;
 
+// Order a wave's LDS accesses for its own other lanes (the LDS executes one
+// wave's accesses in order; this keeps the compiler from reordering them).
+// The helpers below are run by one wave, also inside larger blocks.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ int lanes_below(uint64_t mask) {
   const int lane = threadIdx.x & 63;
   return __popcll(mask & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))));
@@ -97,7 +106,7 @@ __device__ int cell_ranges(const int* ci, int nca, int ncell, bool walls,
     carry += __shfl(incl, 63, 64);
   }
   if (lane == 0) rpre[nr] = carry;
-  __syncthreads();
+  wave_sync();
   return nr;
 }
 
@@ -163,7 +172,7 @@ __device__ bool wave_lsq(int m, const double* P, const double* W, double* A, dou
     A[l] = acc;
   }
   if (lane == 0) *flag = 0;
-  __syncthreads();
+  wave_sync();
   for (int j = 0; j < B; ++j) {
     if (lane == 0) {
       double s = A[tri(j, j)];
@@ -171,14 +180,14 @@ __device__ bool wave_lsq(int m, const double* P, const double* W, double* A, dou
       if (!(s > 0.0)) *flag = 1;
       A[tri(j, j)] = sqrt(s);
     }
-    __syncthreads();
+    wave_sync();
     if (*flag) return false;
     if (lane > j && lane < B) {
       double t = A[tri(lane, j)];
       for (int k = 0; k < j; ++k) t = t - A[tri(lane, k)] * A[tri(j, k)];
       A[tri(lane, j)] = t / A[tri(j, j)];
     }
-    __syncthreads();
+    wave_sync();
   }
   if (lane < NCOL) {
     const int col = col0 + lane;
@@ -199,7 +208,7 @@ __device__ bool wave_lsq(int m, const double* P, const double* W, double* A, dou
       z[i] = s / A[tri(i, i)];
     }
   }
-  __syncthreads();
+  wave_sync();
   return true;
 }
 
@@ -259,7 +268,7 @@ __device__ int value_row(const CloudView& a, const double* xq, ValueRowSm<D>& sm
   for (int t = 0; t < 3; ++t) {
     const bool last = t == 2;
     if (t == 1) {
-      __syncthreads();
+      wave_sync();
       nr = cell_ranges<D, 2>(cb, a.nca, a.ncell, false, a.cstart, sm.rb, sm.rpre);
       total = sm.rpre[nr];
     }
@@ -286,14 +295,14 @@ __device__ int value_row(const CloudView& a, const double* xq, ValueRowSm<D>& sm
       if (in && pos < 256) sm.sel[pos] = j;
       m += __popcll(mask);
     }
-    __syncthreads();
+    wave_sync();
     if (m < D + 2) {
       if (last) return -1;
       continue;
     }
     if (m > a.cap) return -2;
     rank_sorted_store(sm.sel, m, a.cap, sm.srt);
-    __syncthreads();
+    wave_sync();
     for (int e = lane; e < m; e += kWave) {
       const int j = sm.srt[e];
       double y[D], r2 = 0.0;
@@ -305,10 +314,10 @@ __device__ int value_row(const CloudView& a, const double* xq, ValueRowSm<D>& sm
       sm.W[e] = exp(-a.alpha * r2);
       Basis<D, 1>::eval(y, sm.P + e * B);
     }
-    __syncthreads();
+    wave_sync();
     if (!wave_lsq<B, 1>(m, sm.P, sm.W, sm.A, sm.Z, 0, &sm.flag)) {
       if (last) return -1;
-      __syncthreads();
+      wave_sync();
       continue;
     }
     if (last) return m;
@@ -318,7 +327,7 @@ __device__ int value_row(const CloudView& a, const double* xq, ValueRowSm<D>& sm
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) amp = amp + __shfl_xor(amp, o, kWave);
     if (amp <= kValueRowAmp) return m;
-    __syncthreads();   // the next radius reuses the staging arrays
+    wave_sync();   // the next radius reuses the staging arrays
   }
   return -1;
 }

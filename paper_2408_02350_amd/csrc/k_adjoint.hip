@@ -1081,9 +1081,7 @@ hipError_t launch_adjoint_transposes(const Ctx& c) {
   if (c.Nw > 0)
     hipLaunchKernelGGL(k_wt_count, dim3(c.Nw), dim3(64), 0, c.stream, c.Nw, c.cap, c.d.wcnt,
                        c.d.widx, j.wtstart);
-  e = launch_scan(c.stream, j.wtstart, c.N);
-  if (e != hipSuccess) return e;
-  e = launch_copy_i32(c.stream, j.wtstart, j.wtcursor, c.N);
+  e = launch_scan(c, j.wtstart, c.N, j.wtcursor);
   if (e != hipSuccess) return e;
   if (c.Nw > 0)
     hipLaunchKernelGGL(k_wt_scatter, dim3(c.Nw), dim3(64), 0, c.stream, c.Nw, c.cap, c.d.wcnt,

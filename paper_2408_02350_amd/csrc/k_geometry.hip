@@ -23,10 +23,6 @@ __global__ void k_fill_f64(double* p, int64_t n, double v) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
 }
-__global__ void k_copy_i32(const int32_t* __restrict__ s, int32_t* __restrict__ d, int64_t n) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n) d[i] = s[i];
-}
 
 static inline unsigned blocks_for(int64_t n, int t) { return static_cast<unsigned>((n + t - 1) / t); }
 
@@ -38,11 +34,6 @@ hipError_t launch_fill_i32(hipStream_t s, int32_t* p, int64_t n, int32_t v) {
 hipError_t launch_fill_f64(hipStream_t s, double* p, int64_t n, double v) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_fill_f64, dim3(blocks_for(n, 256)), dim3(256), 0, s, p, n, v);
-  return hipGetLastError();
-}
-hipError_t launch_copy_i32(hipStream_t s, const int32_t* src, int32_t* dst, int64_t n) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_copy_i32, dim3(blocks_for(n, 256)), dim3(256), 0, s, src, dst, n);
   return hipGetLastError();
 }
 
@@ -86,72 +77,101 @@ __global__ void k_cell_count(int N, int nca, int ncell, const double* __restrict
   atomicAdd(&count[k], 1);
 }
 
-// Exclusive scan of n int32 in place (one block of 1024 threads walking the
-// array in chunks of 1024*PER); a[n] receives the total.  copy (may be null)
-// receives the same n values.  Each chunk is read and written coalesced
-// through LDS (padded one word in 32 against bank conflicts); each thread
-// scans PER consecutive entries.
-constexpr int kScanPer = 8;
+// Exclusive scan of n int32 in place; a[n] receives the total.  copy (may be
+// null) receives the same n values.  A chunk of 1024 * kScanPer entries is one
+// block's: read and written coalesced through LDS (padded one word in 32
+// against bank conflicts), each thread scanning kScanPer consecutive entries.
+// One chunk takes one launch.  More take two: every block scans its chunk and
+// leaves its sum, then every block adds the sums before its own (a serial
+// walk of the chunks by one block took 29 us at 51842 entries, 44 at 110592;
+// the two launches take 10).
+constexpr int kScanPer = kScanChunk / 1024;
 __device__ __forceinline__ int scan_pad(int i) { return i + (i >> 5); }
 
-__global__ __launch_bounds__(1024) void k_scan_inplace(int32_t* a, int n, int32_t* copy) {
-  constexpr int PER = kScanPer, CH = 1024 * PER;
+__global__ __launch_bounds__(1024) void k_scan_chunk(int32_t* a, int n, int32_t* copy,
+                                                     int32_t* sums) {
+  constexpr int PER = kScanPer, CH = kScanChunk;
   __shared__ int32_t buf[CH + CH / 32];
   __shared__ int32_t wsum[16];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  int carry = 0;
-  for (int base = 0; base < n; base += CH) {
+  const int base = blockIdx.x * CH;
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int i = k * 1024 + tid, g = base + i;
-      buf[scan_pad(i)] = g < n ? a[g] : 0;
-    }
-    __syncthreads();
-    int v[PER];
-    int s = 0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      v[k] = buf[scan_pad(tid * PER + k)];
-      s += v[k];
-    }
-    int incl = s;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int t = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += t;
-    }
-    if (lane == 63) wsum[wid] = incl;
-    __syncthreads();
-    if (wid == 0) {
-      int w = lane < 16 ? wsum[lane] : 0;
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) {
-        const int t = __shfl_up(w, o, 64);
-        if (lane >= o) w += t;
-      }
-      if (lane < 16) wsum[lane] = w;
-    }
-    __syncthreads();
-    int run = carry + (incl - s) + (wid > 0 ? wsum[wid - 1] : 0);
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      buf[scan_pad(tid * PER + k)] = run;
-      run += v[k];
-    }
-    carry += wsum[15];
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int i = k * 1024 + tid, g = base + i;
-      if (g < n) {
-        const int x = buf[scan_pad(i)];
-        a[g] = x;
-        if (copy) copy[g] = x;
-      }
-    }
-    __syncthreads();
+  for (int k = 0; k < PER; ++k) {
+    const int i = k * 1024 + tid, g = base + i;
+    buf[scan_pad(i)] = g < n ? a[g] : 0;
   }
-  if (tid == 0) a[n] = carry;
+  __syncthreads();
+  int v[PER];
+  int s = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    v[k] = buf[scan_pad(tid * PER + k)];
+    s += v[k];
+  }
+  int incl = s;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += t;
+  }
+  if (lane == 63) wsum[wid] = incl;
+  __syncthreads();
+  if (wid == 0) {
+    int w = lane < 16 ? wsum[lane] : 0;
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+      const int t = __shfl_up(w, o, 64);
+      if (lane >= o) w += t;
+    }
+    if (lane < 16) wsum[lane] = w;
+  }
+  __syncthreads();
+  int run = (incl - s) + (wid > 0 ? wsum[wid - 1] : 0);
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    buf[scan_pad(tid * PER + k)] = run;
+    run += v[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = k * 1024 + tid, g = base + i;
+    if (g < n) {
+      const int x = buf[scan_pad(i)];
+      a[g] = x;
+      if (copy) copy[g] = x;
+    }
+  }
+  if (tid == 0) {
+    if (sums) sums[blockIdx.x] = wsum[15];
+    else a[n] = wsum[15];
+  }
+}
+
+__global__ __launch_bounds__(1024) void k_scan_add(int32_t* a, int n, int32_t* copy,
+                                                   const int32_t* __restrict__ sums) {
+  __shared__ int32_t wsum[16];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, nb = gridDim.x;
+  int s = 0;
+  for (int b = tid; b < static_cast<int>(blockIdx.x); b += 1024) s += sums[b];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if (lane == 0) wsum[wid] = s;
+  __syncthreads();
+  int before = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) before += wsum[w];
+  const int base = blockIdx.x * kScanChunk;
+#pragma unroll
+  for (int k = 0; k < kScanPer; ++k) {
+    const int g = base + k * 1024 + tid;
+    if (g < n) {
+      const int x = a[g] + before;
+      a[g] = x;
+      if (copy) copy[g] = x;
+    }
+  }
+  if (tid == 0 && static_cast<int>(blockIdx.x) == nb - 1) a[n] = before + sums[nb - 1];
 }
 
 __global__ void k_cell_scatter(int N, const int32_t* __restrict__ key, int32_t* __restrict__ cursor,
@@ -183,8 +203,14 @@ __global__ void k_cell_rank(int N, int D, const int32_t* __restrict__ key,
   for (int a = 0; a < D; ++a) xs[static_cast<int64_t>(a) * N + dst] = x[static_cast<int64_t>(a) * N + i];
 }
 
-hipError_t launch_scan(hipStream_t s, int32_t* a, int n) {
-  hipLaunchKernelGGL(k_scan_inplace, dim3(1), dim3(1024), 0, s, a, n, nullptr);
+hipError_t launch_scan(const Ctx& c, int32_t* a, int n, int32_t* copy) {
+  const unsigned nb = blocks_for(n, kScanChunk);
+  if (nb <= 1) {
+    hipLaunchKernelGGL(k_scan_chunk, dim3(1), dim3(1024), 0, c.stream, a, n, copy, nullptr);
+  } else {
+    hipLaunchKernelGGL(k_scan_chunk, dim3(nb), dim3(1024), 0, c.stream, a, n, nullptr, c.d.scansum);
+    hipLaunchKernelGGL(k_scan_add, dim3(nb), dim3(1024), 0, c.stream, a, n, copy, c.d.scansum);
+  }
   return hipGetLastError();
 }
 
@@ -199,8 +225,8 @@ hipError_t launch_cells(const Ctx& c, const double* x) {
   else
     hipLaunchKernelGGL(k_cell_count<3>, dim3(blocks_for(c.N, 256)), dim3(256), 0, c.stream, c.N,
                        c.nca, c.ncell, x, d.wall_id, d.key, d.cstart);
-  hipLaunchKernelGGL(k_scan_inplace, dim3(1), dim3(1024), 0, c.stream, d.cstart, nkeys,
-                     d.ccursor);
+  e = launch_scan(c, d.cstart, nkeys, d.ccursor);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_cell_scatter, dim3(blocks_for(c.N, 256)), dim3(256), 0, c.stream, c.N,
                      d.key, d.ccursor, d.cperm2);
   hipLaunchKernelGGL(k_cell_rank, dim3(blocks_for(c.N, 256)), dim3(256), 0, c.stream, c.N, c.D,

@@ -225,11 +225,15 @@ hipEvent_t take_event(Ctx& c) {
 // S1-S3 and the wall rows into the workspace, then the patch unions.
 static int build_geometry(Ctx& c, const double* x) {
   hipError_t e = launch_cells(c, x);
-  if (e == hipSuccess) e = launch_neighbors(c, x, c.d.ncnt, c.d.nidx);
-  if (e == hipSuccess)
-    e = launch_wls(c, x, c.d.ncnt, c.d.nidx, nullptr, c.d.ops64, c.d.ops32, nullptr);
-  if (e == hipSuccess) e = launch_wall_stencil(c, x);
-  if (e == hipSuccess) e = launch_patches(c);
+  if (e == hipSuccess && geometry_small(c)) {
+    e = launch_geometry_small(c, x);
+  } else {
+    if (e == hipSuccess) e = launch_neighbors(c, x, c.d.ncnt, c.d.nidx);
+    if (e == hipSuccess)
+      e = launch_wls(c, x, c.d.ncnt, c.d.nidx, nullptr, c.d.ops64, c.d.ops32, nullptr);
+    if (e == hipSuccess) e = launch_wall_stencil(c, x);
+    if (e == hipSuccess) e = launch_patches(c);
+  }
   c.adj_valid = false;
   c.pm_valid = false;
   if (e != hipSuccess) return hip_fail(&c, e, "geometry launch");
@@ -500,9 +504,8 @@ int step_impl(Ctx& c, const void* f_in, void* f_out, double* x, double* U, doubl
     c.timed.emplace_back(ev0, ev1);
   }
   if (e == hipSuccess && !fused) e = bgk::launch_collide(c, ft, f_out, rho, U, T);
-  if (e == hipSuccess) e = bgk::launch_wall_bc(c, f_out, rho, U, T);
+  if (e == hipSuccess) e = bgk::launch_wall_bc(c, f_out, rho, U, T, c.cfg.move ? x : nullptr);
   if (e == hipSuccess && c.cfg.move) {
-    e = bgk::launch_move(c, x, U);
     c.geom_valid = false;
     c.pm_valid = false;
   }

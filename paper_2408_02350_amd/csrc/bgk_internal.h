@@ -178,6 +178,9 @@ hipError_t launch_wls(const Ctx& c, const double* x, const int32_t* cnt, const i
                       double* grad, double* ops, float* ops32, int32_t* degree);
 hipError_t launch_wall_stencil(const Ctx& c, const double* x);
 hipError_t launch_patches(const Ctx& c);
+// neighbours, operators, unions and wall rows of a small cloud in one launch
+bool geometry_small(const Ctx& c);
+hipError_t launch_geometry_small(const Ctx& c, const double* x);
 hipError_t launch_wall_unions(const Ctx& c);
 // sorted unions of the rows of patches of P entries of plist (n entries,
 // -1 = empty); one wavefront per patch
@@ -197,7 +200,9 @@ hipError_t launch_fused(const Ctx& c, const void* f_in, void* f_out, const doubl
                         void* f_tilde = nullptr);
 hipError_t launch_collide(const Ctx& c, const void* ft, void* fout, double* rho, double* U,
                           double* T);
-hipError_t launch_wall_bc(const Ctx& c, void* f, double* rho, double* U, double* T);
+// x non-null: the interior particles also move (S8), in the same launch
+hipError_t launch_wall_bc(const Ctx& c, void* f, double* rho, double* U, double* T,
+                          double* x = nullptr);
 hipError_t launch_move(const Ctx& c, double* x, const double* U);
 hipError_t launch_moments(const Ctx& c, const void* f, double* rho, double* U, double* T);
 constexpr int kCheckTerms = 12;  // per-particle slots of the state check (and its outputs)

@@ -72,7 +72,7 @@ __device__ int cell_ranges(const int* ci, int nca, int ncell, bool walls,
   constexpr int NC = (D == 2) ? W * W : W * W * W;
   const int parts = walls ? 2 : 1;
   const int nr = NC * parts;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
   int carry = 0;
   for (int r0 = 0; r0 < nr; r0 += kWave) {
     const int r = r0 + lane;
@@ -124,7 +124,7 @@ __device__ __forceinline__ int cand_slot(int c, int nr, const int32_t* rb, const
 // values are distinct particle indices); only ranks < cap are written.
 __device__ __forceinline__ void rank_sorted_store(const int32_t* list, int n, int cap,
                                                   int32_t* __restrict__ row) {
-  for (int s = threadIdx.x; s < n; s += kWave) {
+  for (int s = threadIdx.x & 63; s < n; s += kWave) {
     const int v = list[s];
     int rank = 0;
     for (int q = 0; q < n; ++q) rank += (list[q] < v);
@@ -162,7 +162,7 @@ template <int B, int NCOL>
 __device__ bool wave_lsq(int m, const double* P, const double* W, double* A, double* Z, int col0,
                          int* flag) {
   constexpr int NT = B * (B + 1) / 2;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
   for (int l = lane; l < NT; l += kWave) {
     int r = 0;
     while (tri(r + 1, 0) <= l) ++r;
@@ -256,7 +256,7 @@ __device__ __forceinline__ double value_weight(const ValueRowSm<D>& sm, int e);
 template <int D>
 __device__ int value_row(const CloudView& a, const double* xq, ValueRowSm<D>& sm, double& hb) {
   constexpr int B = D + 1;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
   int cb[D];
 #pragma unroll
   for (int q = 0; q < D; ++q) cb[q] = cell_coord(xq[q], a.nca);

@@ -159,6 +159,49 @@ hipError_t launch_collide(const Ctx& c, const void* ft, void* fout, double* rho,
   return hipGetLastError();
 }
 
+// ------------------------------------------------------------ S8 motion
+struct MoveArgs {
+  int N, D, Ni, blocks;  // blocks of kThreads interior particles
+  double dt, lo, hi;
+  const int32_t* plist;
+  const double* U;
+  double* x;
+  int32_t* err;
+};
+
+__device__ __forceinline__ void move_particle(const MoveArgs& a, int k) {
+  if (k >= a.Ni) return;
+  const int i = a.plist[k];
+  int clamped = 0;
+  for (int q = 0; q < a.D; ++q) {
+    double y = a.x[static_cast<size_t>(q) * a.N + i] + a.dt * a.U[static_cast<size_t>(q) * a.N + i];
+    if (y < a.lo) {
+      y = a.lo;
+      ++clamped;
+    }
+    if (y > a.hi) {
+      y = a.hi;
+      ++clamped;
+    }
+    a.x[static_cast<size_t>(q) * a.N + i] = y;
+  }
+  if (clamped) atomicAdd(&a.err[1], clamped);
+}
+
+__global__ void k_move(const MoveArgs a) { move_particle(a, blockIdx.x * blockDim.x + threadIdx.x); }
+
+static MoveArgs move_of(const Ctx& c, double* x, const double* U) {
+  return MoveArgs{c.N, c.D, c.Ni, (c.Ni + kThreads - 1) / kThreads, c.cfg.dt, 0.1 * c.cfg.dx,
+                  1.0 - 0.1 * c.cfg.dx, c.d.cperm, U, x, c.d.err};
+}
+
+hipError_t launch_move(const Ctx& c, double* x, const double* U) {
+  if (c.Ni == 0) return hipSuccess;
+  const MoveArgs a = move_of(c, x, U);
+  hipLaunchKernelGGL(k_move, dim3(a.blocks), dim3(kThreads), 0, c.stream, a);
+  return hipGetLastError();
+}
+
 // ------------------------------------------------------------ S7 walls
 struct WallBcArgs {
   int N, NV, nv, cap, Nw, D;
@@ -180,6 +223,10 @@ struct WallBcArgs {
   const int32_t* wuj;
   const uint32_t* wue;
   int wucap;
+  // the position update of the interior particles (S8) by the blocks after
+  // the nwb wall blocks: it needs their U, which the walls leave alone
+  int nwb;
+  MoveArgs mv;
 };
 
 // Sum K doubles over a block of nw wavefronts in a fixed order (wavefront
@@ -273,7 +320,12 @@ __global__ __launch_bounds__(kThreads) void k_wall_bc(const WallBcArgs a) {
   double* etab = wtab + nv;
   double* uw = etab + D * nv;
   int32_t* ur = reinterpret_cast<int32_t*>(uw + (P > 1 ? a.wucap * P : 0));
-  const int k = xcd_logical_block(blockIdx.x, gridDim.x);  // neighbouring walls share an L2
+  if (static_cast<int>(blockIdx.x) >= a.nwb) {
+    for (int g = threadIdx.x; g < kThreads; g += blockDim.x)
+      move_particle(a.mv, (blockIdx.x - a.nwb) * kThreads + g);
+    return;
+  }
+  const int k = xcd_logical_block(blockIdx.x, a.nwb);  // neighbouring walls share an L2
   const int nw = blockDim.x >> 6;
   int kt[P], bt[P];  // wall-list slot and particle of each patch entry (-1: empty)
 #pragma unroll
@@ -524,16 +576,18 @@ __global__ __launch_bounds__(kThreads) void k_wall_bc(const WallBcArgs a) {
 }
 
 template <int D, int NC, typename Real, int R>
-static void wall_bc_r(const Ctx& c, const WallBcArgs& a, dim3 t, size_t lds) {
+static void wall_bc_r(const Ctx& c, WallBcArgs a, dim3 t, size_t lds) {
   if constexpr (D == 3) {  // wall patches are formed in 3D only
     if (c.npw > 0) {
       const size_t ul = static_cast<size_t>(c.wucap) * (kWallPatch * sizeof(double) + sizeof(int32_t));
-      hipLaunchKernelGGL((k_wall_bc<D, NC, Real, R, kWallPatch>), dim3(c.npw), t, lds + ul,
-                         c.stream, a);
+      a.nwb = c.npw;
+      hipLaunchKernelGGL((k_wall_bc<D, NC, Real, R, kWallPatch>), dim3(a.nwb + a.mv.blocks), t,
+                         lds + ul, c.stream, a);
       return;
     }
   }
-  hipLaunchKernelGGL((k_wall_bc<D, NC, Real, R, 1>), dim3(c.Nw), t, lds, c.stream, a);
+  a.nwb = c.Nw;
+  hipLaunchKernelGGL((k_wall_bc<D, NC, Real, R, 1>), dim3(a.nwb + a.mv.blocks), t, lds, c.stream, a);
 }
 
 template <int D, int NC, typename Real>
@@ -548,49 +602,19 @@ static void wall_bc_t(const Ctx& c, const WallBcArgs& a) {
   else wall_bc_r<D, NC, Real, 1>(c, a, t, lds);
 }
 
-hipError_t launch_wall_bc(const Ctx& c, void* f, double* rho, double* U, double* T) {
-  if (c.Nw == 0) return hipSuccess;
+hipError_t launch_wall_bc(const Ctx& c, void* f, double* rho, double* U, double* T, double* x) {
+  if (c.Nw == 0) return x ? launch_move(c, x, U) : hipSuccess;
   WallBcArgs a{c.N,          c.NV,      c.cfg.nv,      c.cap,  c.Nw,   c.D,    c.cfg.vmax,
                omega_of(c.cfg), c.lid,  c.cfg.wall_T,  c.d.wall_list, c.d.wall_id, c.d.wcnt,
                c.d.widx,     c.d.wc0,   f,             rho,    U,      T,      c.d.err,
-               c.d.wpl,      c.d.wucount, c.d.wuj,     c.d.wue, c.wucap};
+               c.d.wpl,      c.d.wucount, c.d.wuj,     c.d.wue, c.wucap, 0,
+               x ? move_of(c, x, U) : MoveArgs{}};
   const bool f64 = c.cfg.precision == BGK_FP64;
   if (c.D == 2) {
     if (f64) wall_bc_t<2, 2, double>(c, a); else wall_bc_t<2, 2, float>(c, a);
   } else {
     if (f64) wall_bc_t<3, 1, double>(c, a); else wall_bc_t<3, 1, float>(c, a);
   }
-  return hipGetLastError();
-}
-
-// ------------------------------------------------------------ S8 motion
-__global__ void k_move(int N, int D, int Ni, double dt, double lo, double hi,
-                       const int32_t* __restrict__ plist, const double* __restrict__ U,
-                       double* __restrict__ x, int32_t* __restrict__ err) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= Ni) return;
-  const int i = plist[k];
-  int clamped = 0;
-  for (int a = 0; a < D; ++a) {
-    double y = x[static_cast<size_t>(a) * N + i] + dt * U[static_cast<size_t>(a) * N + i];
-    if (y < lo) {
-      y = lo;
-      ++clamped;
-    }
-    if (y > hi) {
-      y = hi;
-      ++clamped;
-    }
-    x[static_cast<size_t>(a) * N + i] = y;
-  }
-  if (clamped) atomicAdd(&err[1], clamped);
-}
-
-hipError_t launch_move(const Ctx& c, double* x, const double* U) {
-  if (c.Ni == 0) return hipSuccess;
-  const double lo = 0.1 * c.cfg.dx, hi = 1.0 - 0.1 * c.cfg.dx;
-  hipLaunchKernelGGL(k_move, dim3((c.Ni + 255) / 256), dim3(256), 0, c.stream, c.N, c.D, c.Ni,
-                     c.cfg.dt, lo, hi, c.d.cperm, U, x, c.d.err);
   return hipGetLastError();
 }
 

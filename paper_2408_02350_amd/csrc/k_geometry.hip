@@ -203,6 +203,80 @@ __global__ void k_cell_rank(int N, int D, const int32_t* __restrict__ key,
   for (int a = 0; a < D; ++a) xs[static_cast<int64_t>(a) * N + dst] = x[static_cast<int64_t>(a) * N + i];
 }
 
+// The whole cell list of a small cloud in one block: keys, counts, starts and
+// the unsorted permutation live in LDS (2 N + 2 nkeys + 1 words).  Same result
+// as the five launches above, whose launch gaps and ramps cost more than their
+// work there: 8.9 us less per step at 32^2, 7.2 at 64^2, 3.6 at 80^2 and 8.2
+// at 16^3 particles; level at 100^2, 1 us more at 20^3.
+constexpr int kCellsOneMax = 7168;  // particles
+constexpr size_t kCellsOneLds = 150 * 1024;
+template <int D>
+__global__ __launch_bounds__(1024) void k_cells_one(int N, int nca, int ncell,
+                                                    const double* __restrict__ x,
+                                                    const int32_t* __restrict__ wall_id,
+                                                    int32_t* __restrict__ cstart,
+                                                    int32_t* __restrict__ cperm,
+                                                    double* __restrict__ xs) {
+  extern __shared__ int32_t csm[];
+  __shared__ int32_t wsum[16];
+  const int nkeys = 2 * ncell;
+  int32_t* start = csm;               // [nkeys + 1]
+  int32_t* cursor = start + nkeys + 1;  // [nkeys]
+  int32_t* key = cursor + nkeys;      // [N]
+  int32_t* perm2 = key + N;           // [N]
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  for (int k = tid; k < nkeys; k += 1024) cursor[k] = 0;
+  __syncthreads();
+  for (int i = tid; i < N; i += 1024) {
+    int cc[D];
+#pragma unroll
+    for (int a = 0; a < D; ++a) cc[a] = cell_coord(x[static_cast<int64_t>(a) * N + i], nca);
+    const int k = cell_key<D>(cc, nca) + (wall_id[i] != 0 ? ncell : 0);
+    key[i] = k;
+    atomicAdd(&cursor[k], 1);
+  }
+  __syncthreads();
+  // exclusive scan: each thread a run of consecutive keys
+  const int per = (nkeys + 1023) / 1024, k0 = min(tid * per, nkeys), k1 = min(k0 + per, nkeys);
+  int s = 0;
+  for (int k = k0; k < k1; ++k) s += cursor[k];
+  int incl = s;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += t;
+  }
+  if (lane == 63) wsum[wid] = incl;
+  __syncthreads();
+  int run = incl - s;
+  for (int w = 0; w < wid; ++w) run += wsum[w];
+  for (int k = k0; k < k1; ++k) {
+    const int v = cursor[k];
+    start[k] = run;
+    cursor[k] = run;
+    cstart[k] = run;
+    run += v;
+  }
+  if (tid == 0) {
+    start[nkeys] = N;
+    cstart[nkeys] = N;
+  }
+  __syncthreads();
+  for (int i = tid; i < N; i += 1024) perm2[atomicAdd(&cursor[key[i]], 1)] = i;
+  __syncthreads();
+  for (int q = tid; q < N; q += 1024) {
+    const int i = perm2[q], k = key[i];
+    const int b = start[k], e = start[k + 1];
+    int rank = 0;
+    for (int u = b; u < e; ++u) rank += perm2[u] < i;
+    const int dst = b + rank;
+    cperm[dst] = i;
+#pragma unroll
+    for (int a = 0; a < D; ++a)
+      xs[static_cast<int64_t>(a) * N + dst] = x[static_cast<int64_t>(a) * N + i];
+  }
+}
+
 hipError_t launch_scan(const Ctx& c, int32_t* a, int n, int32_t* copy) {
   const unsigned nb = blocks_for(n, kScanChunk);
   if (nb <= 1) {
@@ -217,6 +291,19 @@ hipError_t launch_scan(const Ctx& c, int32_t* a, int n, int32_t* copy) {
 hipError_t launch_cells(const Ctx& c, const double* x) {
   const Dev& d = c.d;
   const int nkeys = 2 * c.ncell;
+  const size_t one = (2 * static_cast<size_t>(c.N) + 2 * nkeys + 1) * sizeof(int32_t);
+  if (c.N <= kCellsOneMax && one <= kCellsOneLds) {
+    auto kf = c.D == 2 ? k_cells_one<2> : k_cells_one<3>;
+    if (one > 64 * 1024) {
+      const hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(kf),
+                                                hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                static_cast<int>(kCellsOneLds));
+      if (ea != hipSuccess) return ea;
+    }
+    hipLaunchKernelGGL(kf, dim3(1), dim3(1024), one, c.stream, c.N, c.nca, c.ncell, x, d.wall_id,
+                       d.cstart, d.cperm, d.xs);
+    return hipGetLastError();
+  }
   hipError_t e = launch_fill_i32(c.stream, d.cstart, nkeys + 1, 0);
   if (e != hipSuccess) return e;
   if (c.D == 2)
@@ -240,65 +327,87 @@ hipError_t launch_cells(const Ctx& c, const double* x) {
 // |x_j - x_i|^2 <= h^2, compact the hits, and store them ascending.
 constexpr int kHitCap = 1024;  // hits kept in LDS (more are only counted)
 
+struct NbrArgs {
+  int N, nca, ncell, cap;
+  double h2;
+  const double* x;
+  const double* xs;
+  const int32_t* cstart;
+  const int32_t* cperm;
+  int32_t* cnt;
+  int32_t* idx;
+  int32_t* err;
+};
+
 template <int D>
-__global__ __launch_bounds__(64) void k_neighbors(int N, int nca, int ncell, double h2, int cap,
-                                                  const double* __restrict__ x,
-                                                  const double* __restrict__ xs,
-                                                  const int32_t* __restrict__ cstart,
-                                                  const int32_t* __restrict__ cperm,
-                                                  int32_t* __restrict__ cnt,
-                                                  int32_t* __restrict__ idx,
-                                                  int32_t* __restrict__ err) {
-  constexpr int NR = (D == 2 ? 9 : 27) * 2;
-  __shared__ int32_t rb[NR], rpre[NR + 1];
-  __shared__ int32_t hits[kHitCap];
-  const int i = blockIdx.x, lane = threadIdx.x;
+struct NbrSm {
+  static constexpr int NR = (D == 2 ? 9 : 27) * 2;
+  int32_t rb[NR], rpre[NR + 1];
+};
+
+// Neighbours of particle i by one wave: the hits (at most hit_cap kept) in
+// hits[], and the sorted row stored.  Returns the true count.
+template <int D>
+__device__ __forceinline__ int neighbor_row(const NbrArgs& a, int i, NbrSm<D>& sm, int32_t* hits,
+                                            int hit_cap) {
+  const int lane = threadIdx.x & 63;
   double xi[D];
   int ci[D];
 #pragma unroll
-  for (int a = 0; a < D; ++a) {
-    xi[a] = x[static_cast<int64_t>(a) * N + i];
-    ci[a] = cell_coord(xi[a], nca);
+  for (int q = 0; q < D; ++q) {
+    xi[q] = a.x[static_cast<int64_t>(q) * a.N + i];
+    ci[q] = cell_coord(xi[q], a.nca);
   }
-  const int nr = cell_ranges<D, 1>(ci, nca, ncell, true, cstart, rb, rpre);
-  const int total = rpre[nr];
+  const int nr = cell_ranges<D, 1>(ci, a.nca, a.ncell, true, a.cstart, sm.rb, sm.rpre);
+  const int total = sm.rpre[nr];
   int m = 0;
   for (int c0 = 0; c0 < total; c0 += kWave) {
     const int cidx = c0 + lane;
     bool hit = false;
     int j = 0;
     if (cidx < total) {
-      const int p = cand_slot(cidx, nr, rb, rpre);
-      j = cperm[p];
+      const int p = cand_slot(cidx, nr, sm.rb, sm.rpre);
+      j = a.cperm[p];
       double r2 = 0.0;
 #pragma unroll
-      for (int a = 0; a < D; ++a) {
-        const double dl = xs[static_cast<int64_t>(a) * N + p] - xi[a];
+      for (int q = 0; q < D; ++q) {
+        const double dl = a.xs[static_cast<int64_t>(q) * a.N + p] - xi[q];
         r2 = r2 + dl * dl;
       }
-      hit = r2 <= h2;
+      hit = r2 <= a.h2;
     }
     const uint64_t mask = __ballot(hit);
     const int pos = m + lanes_below(mask);
-    if (hit && pos < kHitCap) hits[pos] = j;
+    if (hit && pos < hit_cap) hits[pos] = j;
     m += __popcll(mask);
   }
-  __syncthreads();
-  rank_sorted_store(hits, min(m, kHitCap), cap, idx + static_cast<int64_t>(i) * cap);
+  wave_sync();
+  rank_sorted_store(hits, min(m, hit_cap), a.cap, a.idx + static_cast<int64_t>(i) * a.cap);
   if (lane == 0) {
-    cnt[i] = m;
-    if (m > cap) raise_error(err, BGK_ENBR_OVERFLOW);
+    a.cnt[i] = m;
+    if (m > a.cap) raise_error(a.err, BGK_ENBR_OVERFLOW);
   }
+  return m;
+}
+
+template <int D>
+__global__ __launch_bounds__(64) void k_neighbors(const NbrArgs a) {
+  __shared__ NbrSm<D> sm;
+  __shared__ int32_t hits[kHitCap];
+  neighbor_row<D>(a, blockIdx.x, sm, hits, kHitCap);
+}
+
+static NbrArgs nbr_args(const Ctx& c, const double* x, int32_t* cnt, int32_t* idx) {
+  return NbrArgs{c.N, c.nca, c.ncell, c.cap, c.cfg.h * c.cfg.h, x, c.d.xs, c.d.cstart, c.d.cperm,
+                 cnt, idx, c.d.err};
 }
 
 hipError_t launch_neighbors(const Ctx& c, const double* x, int32_t* cnt, int32_t* idx) {
-  const double h2 = c.cfg.h * c.cfg.h;
+  const NbrArgs a = nbr_args(c, x, cnt, idx);
   if (c.D == 2)
-    hipLaunchKernelGGL(k_neighbors<2>, dim3(c.N), dim3(kWave), 0, c.stream, c.N, c.nca, c.ncell,
-                       h2, c.cap, x, c.d.xs, c.d.cstart, c.d.cperm, cnt, idx, c.d.err);
+    hipLaunchKernelGGL(k_neighbors<2>, dim3(c.N), dim3(kWave), 0, c.stream, a);
   else
-    hipLaunchKernelGGL(k_neighbors<3>, dim3(c.N), dim3(kWave), 0, c.stream, c.N, c.nca, c.ncell,
-                       h2, c.cap, x, c.d.xs, c.d.cstart, c.d.cperm, cnt, idx, c.d.err);
+    hipLaunchKernelGGL(k_neighbors<3>, dim3(c.N), dim3(kWave), 0, c.stream, a);
   return hipGetLastError();
 }
 
@@ -416,16 +525,16 @@ __device__ __forceinline__ void wls_basis(int deg, const double* y, double* p) {
 constexpr int kWlsGroup = 4;
 constexpr int kWlsRow = kWave / kWlsGroup;
 
-template <int D>
-__global__ __launch_bounds__(64) void k_wls(const WlsArgs a) {
-  extern __shared__ double wls_sm[];
+// One wave's rows; nbr(i, e): entry e of particle i's neighbour row (i's m
+// entries); wls_sm: wls_smem bytes of LDS.
+template <int D, typename Count, typename Nbr>
+__device__ __forceinline__ void wls_rows(const WlsArgs& a, int pidx, bool valid, Count&& count,
+                                         Nbr&& nbr, double* wls_sm) {
   constexpr int B2 = Basis<D, 2>::B, NT2 = Basis<D, 2>::NT, DD = D * D;
   constexpr int L = kWlsRow;
-  const int lane = threadIdx.x, g = lane / L, gl = lane % L;
-  const int pidx = blockIdx.x * kWlsGroup + g;
-  const bool valid = pidx < a.Ni;
+  const int lane = threadIdx.x & 63, gl = lane % L;
   const int i = valid ? a.plist[pidx] : 0;
-  const int m = valid ? min(a.cnt[i], a.cap) : 0;
+  const int m = valid ? min(count(i), a.cap) : 0;
   int deg = a.deg_cfg;
   if (deg == 2 && m < 2 * B2) deg = 1;
   const int Bg = (deg == 2) ? B2 : (deg == 1 ? D + 1 : D);
@@ -444,7 +553,7 @@ __global__ __launch_bounds__(64) void k_wls(const WlsArgs a) {
 #pragma unroll
   for (int t = 0; t < NT2; ++t) A[t] = 0.0;
   for (int q = 0, e = gl; e < m; ++q, e += L) {
-    const int j = a.idx[row + e];
+    const int j = nbr(i, e);
     double y[D], r2 = 0.0;
 #pragma unroll
     for (int k = 0; k < D; ++k) {
@@ -574,6 +683,15 @@ __global__ __launch_bounds__(64) void k_wls(const WlsArgs a) {
   }
 }
 
+template <int D>
+__global__ __launch_bounds__(64) void k_wls(const WlsArgs a) {
+  extern __shared__ double wls_dyn[];
+  const int pidx = blockIdx.x * kWlsGroup + threadIdx.x / kWlsRow;
+  wls_rows<D>(
+      a, pidx, pidx < a.Ni, [&](int i) { return a.cnt[i]; },
+      [&](int i, int e) { return a.idx[static_cast<int64_t>(i) * a.cap + e]; }, wls_dyn);
+}
+
 static size_t wls_smem(int D, int cap) {
   const size_t qmax = static_cast<size_t>((cap + kWlsRow - 1) / kWlsRow);
   return qmax * kWave * ((D + 1) * sizeof(double) + sizeof(int32_t));
@@ -608,9 +726,8 @@ struct WallArgs {
 };
 
 template <int D>
-__global__ __launch_bounds__(64) void k_wall_stencil(const WallArgs a) {
-  __shared__ ValueRowSm<D> sm;
-  const int k = blockIdx.x, lane = threadIdx.x;
+__device__ __forceinline__ void wall_row(const WallArgs& a, int k, ValueRowSm<D>& sm) {
+  const int lane = threadIdx.x & 63;
   const int b = a.wall_list[k];
   double xb[D];
 #pragma unroll
@@ -631,6 +748,12 @@ __global__ __launch_bounds__(64) void k_wall_stencil(const WallArgs a) {
     a.wc0[row + e] = value_weight<D>(sm, e);
   }
   if (lane == 0) a.wcnt[k] = m;
+}
+
+template <int D>
+__global__ __launch_bounds__(64) void k_wall_stencil(const WallArgs a) {
+  __shared__ ValueRowSm<D> sm;
+  wall_row<D>(a, blockIdx.x, sm);
 }
 
 CloudView cloud_view(const Ctx& c, const double* x) {
@@ -699,70 +822,72 @@ __device__ __forceinline__ int lower_bound_i(const int32_t* v, int n, int x) {
   return lo;
 }
 
-__global__ __launch_bounds__(64) void k_patches(int Ni, int P, int cap, int ucap, int drop_self,
-                                                const int32_t* __restrict__ plist,
-                                                const int32_t* __restrict__ cnt,
-                                                const int32_t* __restrict__ idx,
-                                                int32_t* __restrict__ ucount,
-                                                int32_t* __restrict__ uj, uint32_t* __restrict__ ue,
-                                                int32_t* __restrict__ err) {
-  extern __shared__ int32_t psm[];
+struct UnionSm {
+  int32_t rn[kPatchMax], spt[kPatchMax], m[kPatchMax], self[kPatchMax], pre[kPatchMax + 1];
+};
+
+// The union of patch p's rows by one wave; entry(i, e): entry e of row i;
+// psm: 4 P cap words of LDS.
+template <typename Count, typename Entry>
+__device__ __forceinline__ void merge_rows(int p, int Ni, int P, int cap, int ucap, int drop_self,
+                                           const int32_t* __restrict__ plist, Count&& count,
+                                           Entry&& entry, int32_t* psm, UnionSm& sm,
+                                           int32_t* __restrict__ ucount, int32_t* __restrict__ uj,
+                                           uint32_t* __restrict__ ue) {
   int32_t* rj = psm;                        // [P][cap] neighbour j (self removed)
   int32_t* re = rj + P * cap;          // [P][cap] its slot in the full row
   int32_t* mj = re + P * cap;          // [P*cap] merged j
   int32_t* mt = mj + P * cap;          // merged (slot t << 8 | e)
-  __shared__ int32_t rn[kPatchMax], spt[kPatchMax], sm_[kPatchMax], sself[kPatchMax], spre[kPatchMax + 1];
-  const int p = blockIdx.x, lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
   if (lane < P) {
     const int g = p * P + lane;
     const int pt = g < Ni ? plist[g] : -1;
-    spt[lane] = pt;
-    sm_[lane] = pt >= 0 ? min(cnt[pt], cap) : 0;
-    sself[lane] = 0;
+    sm.spt[lane] = pt;
+    sm.m[lane] = pt >= 0 ? min(count(pt, lane), cap) : 0;
+    sm.self[lane] = 0;
   }
-  __syncthreads();
+  wave_sync();
   // self is in its row exactly once (at most once if the row overflowed):
   // find it in all rows at once, then copy the rows without it
   for (int w = lane; w < P * cap; w += kWave) {
     const int t = w / cap, e = w - t * cap;
-    if (drop_self && e < sm_[t] && idx[static_cast<int64_t>(spt[t]) * cap + e] == spt[t])
-      sself[t] = e + 1;
+    if (drop_self && e < sm.m[t] && entry(sm.spt[t], t, e) == sm.spt[t]) sm.self[t] = e + 1;
   }
-  __syncthreads();
+  wave_sync();
   for (int w = lane; w < P * cap; w += kWave) {
     const int t = w / cap, e = w - t * cap;
-    if (e >= sm_[t]) continue;
-    const int sp = sself[t] - 1;
+    if (e >= sm.m[t]) continue;
+    const int sp = sm.self[t] - 1;
     if (e == sp) continue;
     const int o = (sp >= 0 && e > sp) ? e - 1 : e;
-    rj[t * cap + o] = idx[static_cast<int64_t>(spt[t]) * cap + e];
+    rj[t * cap + o] = entry(sm.spt[t], t, e);
     re[t * cap + o] = e;
   }
-  if (lane < P) rn[lane] = sself[lane] ? sm_[lane] - 1 : sm_[lane];
-  __syncthreads();
+  if (lane < P) sm.rn[lane] = sm.self[lane] ? sm.m[lane] - 1 : sm.m[lane];
+  wave_sync();
   if (lane == 0) {
-    spre[0] = 0;
-    for (int t = 0; t < P; ++t) spre[t + 1] = spre[t] + rn[t];
+    sm.pre[0] = 0;
+    for (int t = 0; t < P; ++t) sm.pre[t + 1] = sm.pre[t] + sm.rn[t];
   }
-  __syncthreads();
-  const int total = spre[P];
+  wave_sync();
+  const int total = sm.pre[P];
   // merged position of every (t, q): q plus, in each other row, the entries
   // before it (equal j in a lower slot t first)
   for (int w = lane; w < total; w += kWave) {
     int t = 0;
-    while (w >= spre[t + 1]) ++t;
-    const int q = w - spre[t];
+    while (w >= sm.pre[t + 1]) ++t;
+    const int q = w - sm.pre[t];
     const int j = rj[t * cap + q];
     int pos = q;
     for (int s2 = 0; s2 < P; ++s2) {
       if (s2 == t) continue;
       const int* v = rj + s2 * cap;
-      pos += (s2 < t) ? lower_bound_i(v, rn[s2], j + 1) : lower_bound_i(v, rn[s2], j);
+      pos += (s2 < t) ? lower_bound_i(v, sm.rn[s2], j + 1) : lower_bound_i(v, sm.rn[s2], j);
     }
     mj[pos] = j;
     mt[pos] = (t << 8) | re[t * cap + q];
   }
-  __syncthreads();
+  wave_sync();
   int nu = 0;
   for (int c0 = 0; c0 < total; c0 += kWave) {
     const int q = c0 + lane;
@@ -785,6 +910,21 @@ __global__ __launch_bounds__(64) void k_patches(int Ni, int P, int cap, int ucap
   if (lane == 0) ucount[p] = min(nu, ucap);
 }
 
+__global__ __launch_bounds__(64) void k_patches(int Ni, int P, int cap, int ucap, int drop_self,
+                                                const int32_t* __restrict__ plist,
+                                                const int32_t* __restrict__ cnt,
+                                                const int32_t* __restrict__ idx,
+                                                int32_t* __restrict__ ucount,
+                                                int32_t* __restrict__ uj,
+                                                uint32_t* __restrict__ ue) {
+  extern __shared__ int32_t psm[];
+  __shared__ UnionSm sm;
+  merge_rows(
+      blockIdx.x, Ni, P, cap, ucap, drop_self, plist, [&](int i, int) { return cnt[i]; },
+      [&](int i, int, int e) { return idx[static_cast<int64_t>(i) * cap + e]; }, psm, sm, ucount,
+      uj, ue);
+}
+
 hipError_t launch_unions(const Ctx& c, int P, int n, const int32_t* plist, const int32_t* cnt,
                          const int32_t* idx, int drop_self, int ucap, int32_t* ucount,
                          int32_t* uj, uint32_t* ue) {
@@ -792,7 +932,7 @@ hipError_t launch_unions(const Ctx& c, int P, int n, const int32_t* plist, const
   if (P < 1 || P > kPatchMax || ucap < P * c.cap) return hipErrorInvalidValue;
   const size_t sm = static_cast<size_t>(4) * P * c.cap * sizeof(int32_t);
   hipLaunchKernelGGL(k_patches, dim3((n + P - 1) / P), dim3(kWave), sm, c.stream, n, P, c.cap,
-                     ucap, drop_self, plist, cnt, idx, ucount, uj, ue, c.d.err);
+                     ucap, drop_self, plist, cnt, idx, ucount, uj, ue);
   return hipGetLastError();
 }
 
@@ -804,6 +944,114 @@ hipError_t launch_patches(const Ctx& c) {
 hipError_t launch_wall_unions(const Ctx& c) {
   return launch_unions(c, kWallPatch, c.npw * kWallPatch, c.d.wpl, c.d.wcnt, c.d.widx, 0,
                        c.wucap, c.d.wucount, c.d.wuj, c.d.wue);
+}
+
+// ------------------------------------------------------------ small clouds
+// S1-S3, the patch unions and the wall rows in one launch.  The first npatch
+// blocks own a patch each: wave t finds the neighbours of the patch's particle
+// t (row to global memory and LDS), then wave 0 solves the least squares of
+// all of them (a 16-lane row each) while wave 1 merges their rows.  The
+// blocks after them take one wall particle per wave: its value row, then (the
+// second Nw) its neighbours.  The same device code, hence the same results,
+// as the four separate kernels.
+struct GeomArgs {
+  NbrArgs n;
+  WlsArgs w;
+  WallArgs wl;
+  int Nw, npatch, ucap;
+  int32_t* ucount;
+  int32_t* uj;
+  uint32_t* ue;
+  size_t off_rows, off_wls, off_psm;  // LDS offsets of a patch block
+};
+
+template <int D, int P>
+__global__ __launch_bounds__(256) void k_geom_small(const GeomArgs a) {
+  extern __shared__ __align__(16) unsigned char gsm[];
+  const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63, cap = a.n.cap;
+  const int b = blockIdx.x;
+  if (b < a.npatch) {
+    __shared__ NbrSm<D> nsm[P];
+    __shared__ UnionSm usm;
+    __shared__ int32_t rows_m[P];
+    int32_t* hits = reinterpret_cast<int32_t*>(gsm);               // [P][256]
+    int32_t* rows = reinterpret_cast<int32_t*>(gsm + a.off_rows);  // [P][cap], sorted
+    if (wid < P) {
+      const int g = b * P + wid;
+      int m = 0;
+      if (g < a.w.Ni) {
+        m = neighbor_row<D>(a.n, a.w.plist[g], nsm[wid], hits + 256 * wid, 256);
+        rank_sorted_store(hits + 256 * wid, min(m, 256), cap, rows + cap * wid);
+      }
+      if (lane == 0) rows_m[wid] = m;
+    }
+    __syncthreads();
+    if (wid == 0) {
+      const int g = lane / kWlsRow, pidx = b * P + g;
+      const int gr = g < P ? g : 0;
+      wls_rows<D>(
+          a.w, pidx, g < P && pidx < a.w.Ni, [&](int) { return rows_m[gr]; },
+          [&](int, int e) { return rows[cap * gr + e]; },
+          reinterpret_cast<double*>(gsm + a.off_wls));
+    } else if (wid == 1) {
+      merge_rows(
+          b, a.w.Ni, P, cap, a.ucap, 1, a.w.plist, [&](int, int t) { return rows_m[t]; },
+          [&](int, int t, int e) { return rows[cap * t + e]; },
+          reinterpret_cast<int32_t*>(gsm + a.off_psm), usm, a.ucount, a.uj, a.ue);
+    }
+  } else {
+    const int k = (b - a.npatch) * 4 + wid;
+    // each wave's LDS is its own ValueRowSm, which also holds a search's
+    static_assert(sizeof(NbrSm<D>) + 256 * sizeof(int32_t) <= sizeof(ValueRowSm<D>), "LDS of a wave");
+    unsigned char* own = gsm + sizeof(ValueRowSm<D>) * wid;
+    if (k < a.Nw) {
+      wall_row<D>(a.wl, k, *reinterpret_cast<ValueRowSm<D>*>(own));
+    } else if (k < 2 * a.Nw) {
+      neighbor_row<D>(a.n, a.wl.wall_list[k - a.Nw], *reinterpret_cast<NbrSm<D>*>(own),
+                      reinterpret_cast<int32_t*>(own + sizeof(NbrSm<D>)), 256);
+    }
+  }
+}
+
+template <int D, int P>
+static hipError_t launch_geom_t(const Ctx& c, GeomArgs a) {
+  auto up = [](size_t v) { return (v + 15) / 16 * 16; };
+  a.off_rows = up(static_cast<size_t>(P) * 256 * sizeof(int32_t));
+  a.off_wls = up(a.off_rows + static_cast<size_t>(P) * c.cap * sizeof(int32_t));
+  a.off_psm = up(a.off_wls + wls_smem(D, c.cap));
+  const size_t patch = a.off_psm + static_cast<size_t>(4) * P * c.cap * sizeof(int32_t);
+  const size_t lds = std::max(patch, 4 * sizeof(ValueRowSm<D>));
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_geom_small<D, P>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             static_cast<int>(lds));
+    if (e != hipSuccess) return e;
+  }
+  const unsigned nb = c.npatch + blocks_for(2 * static_cast<int64_t>(c.Nw), 4);
+  if (nb == 0) return hipSuccess;
+  hipLaunchKernelGGL((k_geom_small<D, P>), dim3(nb), dim3(256), lds, c.stream, a);
+  return hipGetLastError();
+}
+
+// Where one launch beats four (us per step): 14.2 less at 32^2, 4.9 at 64^2,
+// 3.4 at 80^2, 30.8 at 12^3 and 12.7 at 16^3 particles (h = 3.1 dx: 35 at 12^3,
+// 7.6 at 16^3); 7.9 more at 100^2 and 10.1 at 20^3, where the four kernels
+// each fill the chip.
+bool geometry_small(const Ctx& c) { return c.N <= (c.D == 2 ? 7168 : 5120); }
+
+hipError_t launch_geometry_small(const Ctx& c, const double* x) {
+  const Dev& d = c.d;
+  GeomArgs a{nbr_args(c, x, d.ncnt, d.nidx),
+             WlsArgs{c.N, c.cap, c.Ni, c.cfg.wls_degree, c.cfg.h, c.cfg.alpha, x, d.cperm, d.ncnt,
+                     d.nidx, nullptr, d.ops64, d.ops32, nullptr, d.err},
+             WallArgs{cloud_view(c, x), d.wall_list, d.wcnt, d.widx, d.wc0, d.whb, d.err},
+             c.Nw, c.npatch, c.ucap, d.ucount, d.uj, d.ue, 0, 0, 0};
+  hipError_t e = hipSuccess;
+  if (c.D == 2)
+    e = c.tp == 2 ? launch_geom_t<2, 2>(c, a) : launch_geom_t<2, 4>(c, a);
+  else
+    e = launch_geom_t<3, 4>(c, a);
+  return e == hipSuccess ? launch_wall_unions(c) : e;
 }
 
 }  // namespace bgk

@@ -1,0 +1,57 @@
+"""The one-launch cell list and geometry of small clouds, and the position
+update in the wall launch: one moving step against the oracle on both sides of
+the size limits (2D 7168 particles, 3D 5120 and 7168), and the data errors
+raised from inside a step."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2408_02350_amd.bgk as bgk
+from paper_2408_02350_amd.inputs import CavityConfig, make_cloud
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+TOL = {"fp64": 1e-12, "fp32": 1e-5}  # of the field's maximum: one step's rounding
+
+
+def t(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+@pytest.mark.parametrize("dim,n,nv,h,deg,precision", [
+    (2, 4, 4, 2.5, 1, "fp64"), (2, 84, 2, 2.5, 2, "fp64"), (2, 85, 2, 2.5, 2, "fp64"),
+    (2, 30, 4, 3.1, 0, "fp32"), (3, 5, 2, 2.2, 1, "fp64"), (3, 17, 2, 2.2, 2, "fp64"),
+    (3, 18, 2, 2.2, 2, "fp64"), (3, 20, 2, 2.2, 2, "fp64"), (3, 10, 4, 3.1, 0, "fp32")])
+def test_moving_step_around_the_size_limits(dim, n, nv, h, deg, precision):
+    cav = CavityConfig("small", dim, n, nv, 4.0, h, 1.0, 0.2, 1, 1, wls_degree=deg)
+    c = oracle.config(cav)
+    x, wid = make_cloud(dim, n, 3)
+    U0 = np.stack([0.1 * np.sin(np.pi * x[1])] + [0.05 * np.cos(np.pi * x[a])
+                                                  for a in range(1, dim)])
+    f = oracle.maxwellian(c, 1.0 + 0.1 * x[0], U0, 1.0 + 0.05 * x[dim - 1])
+    ctx = bgk.bgk_init(bgk.config_from(cav, precision), t(wid))
+    ft = t(f).to(bgk.f_dtype(ctx.cfg))
+    f = ft.double().cpu().numpy()
+    _, U, _ = oracle.moments(c, f)
+    print(f"case {dim}D n={n} nv={nv} h={h} deg={deg} {precision}", flush=True)
+    xt, Ut, out = t(x), t(U), torch.empty_like(ft)
+    rho, T = torch.empty_like(xt[0]), torch.empty_like(xt[0])
+    bgk.bgk_step(ctx, ft, out, xt, Ut, rho, T)
+    bgk.bgk_check(ctx)
+    rx, rf, rU, rr, rT, _ = oracle.run(c, wid, x, f, U, 1)
+    for got, want in ((out.double(), rf), (xt, rx), (Ut, rU), (rho, rr), (T, rT)):
+        assert np.abs(got.cpu().numpy() - want).max() <= TOL[precision] * max(1.0, np.abs(want).max())
+    assert bgk.bgk_diagnostics(ctx)["max_neighbors_seen"] == oracle.neighbors(c, x)[0].max()
+
+
+@pytest.mark.parametrize("dim,cap,code", [(2, 10, bgk.BGK_ENBR_OVERFLOW), (3, 12, bgk.BGK_ENBR_OVERFLOW)])
+def test_overflow_inside_a_small_step(dim, cap, code):
+    cav = CavityConfig("over", dim, 9, 4, 4.0, 2.5 if dim == 2 else 2.2, 1.0, 0.1, 1, 1)
+    x, wid = make_cloud(dim, 9, 0)
+    ctx = bgk.bgk_init(bgk.config_from(cav, "fp64", max_neighbors=cap), t(wid))
+    bgk.bgk_geometry(ctx, t(x))
+    with pytest.raises(bgk.BgkError) as e:
+        bgk.bgk_check(ctx)
+    assert e.value.code == code
+    bgk.bgk_check(ctx)

@@ -198,6 +198,9 @@ bool use_fused(const Ctx& c);
 hipError_t launch_fused(const Ctx& c, const void* f_in, void* f_out, const double* U_in,
                         double* rho, double* U_out, double* T, bool fuse,
                         void* f_tilde = nullptr);
+// S4 in 3D FP64 by slabs of velocities (f-tilde only; launch_collide finishes)
+bool walk_supported(const Ctx& c);
+hipError_t launch_walk(const Ctx& c, const void* f_in, void* ft, const double* U);
 hipError_t launch_collide(const Ctx& c, const void* ft, void* fout, double* rho, double* U,
                           double* T);
 // x non-null: the interior particles also move (S8), in the same launch

@@ -242,71 +242,6 @@ __global__ __launch_bounds__(kThreads) void k_adj_wall(const AdjArgs<Real> a) {
 }
 
 // ------------------------------------------------------------ S5-S6 adjoint
-// Row loads and stores of R consecutive values as 16-byte (or 8-byte)
-// vectors; the row offsets the callers pass are multiples of R.
-template <typename Real, int R>
-__device__ __forceinline__ void load_rs(const Real* __restrict__ p, Real (&o)[R]) {
-  constexpr int B = R * static_cast<int>(sizeof(Real));
-  constexpr int W = B % 16 == 0 ? 16 / static_cast<int>(sizeof(Real))
-                                : (B % 8 == 0 ? 8 / static_cast<int>(sizeof(Real)) : 1);
-  typedef Real V __attribute__((ext_vector_type(W)));
-  const V* pv = reinterpret_cast<const V*>(__builtin_assume_aligned(p, W * sizeof(Real)));
-#pragma unroll
-  for (int i = 0; i < R / W; ++i) {
-    const V x = pv[i];
-#pragma unroll
-    for (int w = 0; w < W; ++w) o[i * W + w] = x[w];
-  }
-}
-
-template <typename Real, int R>
-__device__ __forceinline__ void store_rs(Real* __restrict__ p, const Real (&o)[R]) {
-  constexpr int B = R * static_cast<int>(sizeof(Real));
-  constexpr int W = B % 16 == 0 ? 16 / static_cast<int>(sizeof(Real))
-                                : (B % 8 == 0 ? 8 / static_cast<int>(sizeof(Real)) : 1);
-  typedef Real V __attribute__((ext_vector_type(W)));
-  V* pv = reinterpret_cast<V*>(__builtin_assume_aligned(p, W * sizeof(Real)));
-#pragma unroll
-  for (int i = 0; i < R / W; ++i) {
-    V x;
-#pragma unroll
-    for (int w = 0; w < W; ++w) x[w] = o[i * W + w];
-    pv[i] = x;
-  }
-}
-
-// Digits of a group of R consecutive nodes along the fastest velocity axis:
-// k[0] counts groups (nv/R per row of that axis), k[1..] are node indices.
-// Advanced by the digits of a fixed stride, with no division per group.
-template <int D>
-struct GroupDigits {
-  int k[D], st[D];
-  __device__ void init(int g, int stride, int ng0, int nv) {
-    k[0] = g % ng0;
-    g /= ng0;
-    st[0] = stride % ng0;
-    stride /= ng0;
-#pragma unroll
-    for (int a = 1; a < D; ++a) {
-      k[a] = g % nv;
-      g /= nv;
-      st[a] = stride % nv;
-      stride /= nv;
-    }
-  }
-  __device__ void advance(int ng0, int nv) {  // (the carry out of the last
-    int x = k[0] + st[0];                      //  digit is past the grid)
-    int carry = x >= ng0;
-    k[0] = carry ? x - ng0 : x;
-#pragma unroll
-    for (int a = 1; a < D; ++a) {
-      x = k[a] + st[a] + carry;
-      carry = x >= nv;
-      k[a] = carry ? x - nv : x;
-    }
-  }
-};
-
 // One block per interior particle.  A thread takes groups of R consecutive
 // nodes along the fastest velocity axis (group g = tid + m kThreads), so the
 // rows move as 16-byte vectors and the factors of the slower axes are formed

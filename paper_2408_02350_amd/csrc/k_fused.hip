@@ -35,9 +35,9 @@
 // is written once.
 //
 // When N_v does not fit one block at the register budget of the precision
-// (large 3D grids in FP64) the velocity range is split into tiles over
-// several blocks; the kernel then writes f-tilde and the separate
-// relaxation kernel finishes the step.
+// the velocity range is split into tiles over several blocks; the kernel then
+// writes f-tilde and the separate relaxation kernel finishes the step (3D
+// FP64: k_walk forms f-tilde instead).
 #include <type_traits>
 
 #include "device_common.h"
@@ -944,11 +944,12 @@ __global__ __launch_bounds__(1024) void k_fused(const FusedArgs a) {
 //    in full.  500^2 x 20^2 FP32 R 4 1183, 2 1377; 300^2 x 16^2 R 4 209, 1
 //    286; 150^2 x 14^2 FP64 R 2 84, 1 114.
 //
-// One tile runs the fused relaxation.  Several FP64 tiles whose f-tilde (all
-// but the last tile) fits the LDS next to the kernel's own tables are walked
-// in turn by one block per patch (inlds), which then relaxes them; otherwise
-// each tile is a block that writes f-tilde, and the separate relaxation
-// kernel finishes.
+// One tile runs the fused relaxation.  Several tiles in 3D FP64 are left to
+// k_walk.  In 2D, several FP64 tiles whose f-tilde (all but the last tile) fits
+// the LDS next to the kernel's own tables are walked in turn by one block per
+// patch (inlds), which then relaxes them.  Otherwise each tile is a block
+// that writes f-tilde.  k_walk and the latter are finished by the separate
+// relaxation kernel.
 struct FusedPlan {
   int R = 0, RB = 0, tiles = 0, bte = 0;
   bool inlds = false;
@@ -956,8 +957,8 @@ struct FusedPlan {
 };
 
 // LDS of one gfx950 workgroup, and what the fused kernel declares
-// statically (upper bound over the instantiations that take inlds: 3D FP64
-// and 2D FP64 with 2- or 4-particle patches)
+// statically (upper bound over the instantiations that take inlds: 2D FP64
+// with 2- or 4-particle patches)
 constexpr size_t kLdsBytes = 160 * 1024;
 constexpr size_t kFusedStaticLds = 34 * 1024;
 
@@ -966,8 +967,7 @@ constexpr size_t kFusedStaticLds = 34 * 1024;
 template <int D, int MODE, int TP, int R, int RB>
 constexpr bool fused_instance() {
   if (MODE == BGK_FP64)
-    return R == RB &&
-           (R == 1 || R == 2 || (D == 3 && R == 3) || (R == 4 && !(D == 2 && TP == 4)));
+    return R == RB && (R == 1 || R == 2 || (R == 4 && !(D == 2 && TP == 4)));
   if (TP != 4) return false;
   if (D == 2)
     return (R == RB && (R == 1 || R == 2 || R == 4)) ||
@@ -998,7 +998,6 @@ static bool with_fused_r(int R, int RB, F&& f) {
   };
   row(std::integral_constant<int, 1>{});
   row(std::integral_constant<int, 2>{});
-  row(std::integral_constant<int, 3>{});
   row(std::integral_constant<int, 4>{});
   row(std::integral_constant<int, 5>{});
   row(std::integral_constant<int, 6>{});
@@ -1061,9 +1060,8 @@ static FusedPlan plan_fused(const Ctx& c) {
   const int lanes = NV / p.R;
   p.tiles = (lanes + 1023) / 1024;
   p.bte = (lanes + p.tiles - 1) / p.tiles;
-  if (f64 && p.tiles > 1) {
-    const size_t nc = D == 2 ? 2 : 1;
-    p.lds = static_cast<size_t>(p.tiles - 1) * c.tp * p.R * nc * p.bte * sizeof(double);
+  if (f64 && D == 2 && p.tiles > 1) {
+    p.lds = static_cast<size_t>(p.tiles - 1) * c.tp * p.R * 2 * p.bte * sizeof(double);
     p.inlds = p.lds + kFusedStaticLds <= kLdsBytes;
   }
   return p;
@@ -1075,7 +1073,7 @@ template <int D, int NC, int MODE, bool FUSE, int TP>
 static hipError_t launch_fused_t(const Ctx& c, FusedArgs a, const FusedPlan& p) {
   a.bte = p.bte;
   a.dvs = 2.0 * c.cfg.vmax / (c.cfg.nv - 1);
-  const bool inlds = FUSE && MODE == BGK_FP64 && p.tiles > 1 && p.inlds;
+  const bool inlds = FUSE && MODE == BGK_FP64 && D == 2 && p.tiles > 1 && p.inlds;
   a.ntl = inlds ? p.tiles : 1;
   const int bt = (a.bte + 63) / 64 * 64;
   dim3 g(c.npatch * (inlds ? 1 : p.tiles)), b(bt);
@@ -1091,7 +1089,7 @@ static hipError_t launch_fused_t(const Ctx& c, FusedArgs a, const FusedPlan& p) 
   };
   const bool known = with_fused_r<D, MODE, TP>(p.R, p.RB, [&](auto r, auto rb) {
     constexpr int R = decltype(r)::value, RB = decltype(rb)::value;
-    if constexpr (FUSE && MODE == BGK_FP64) {
+    if constexpr (FUSE && MODE == BGK_FP64 && D == 2) {
       if (inlds) {
         launch(k_fused<D, NC, MODE, R, RB, FUSE, TP, true>);
         return;
@@ -1130,6 +1128,12 @@ hipError_t launch_fused(const Ctx& c, const void* f_in, void* f_out, const doubl
   if (c.npatch == 0) return hipSuccess;
   const FusedPlan p = plan_fused(c);
   if (p.R == 0) return hipErrorInvalidValue;
+  if (p.tiles > 1 && walk_supported(c)) {
+    void* ft = (fuse && f_tilde) ? f_tilde : f_out;
+    hipError_t e = launch_walk(c, f_in, ft, U_in);
+    if (e == hipSuccess && fuse) e = launch_collide(c, ft, f_out, rho, U_out, T);
+    return e;
+  }
   FusedArgs a{c.N, c.NV, c.cfg.nv, c.cap, c.Ni, c.npatch, c.ucap, 0,
               c.cfg.vmax, c.cfg.dt, c.cfg.kn, omega_fused(c.cfg), 0.0,
               f_in, f_out, U_in,

@@ -583,7 +583,7 @@ __global__ __launch_bounds__(64) void k_adj_transport_wall(const AdjArgs<Real> a
 // per-velocity increments and their sum, so the walk adds instead of
 // multiplying) and read with wave-uniform addresses; each lane loads the
 // two rows an entry needs (f^n_i for the U-derivative, lam_ft_i for the
-// transposed term) one entry ahead, once for all P particles.  The
+// transposed term) once for all P particles.  The
 // per-velocity arithmetic is in the storage precision (FP32 storage: FP32
 // arithmetic, half the registers of FP64 and within that storage's
 // rounding); each lane's lam_U sums are folded per edge and reduced over the
@@ -591,11 +591,18 @@ __global__ __launch_bounds__(64) void k_adj_transport_wall(const AdjArgs<Real> a
 // g.w - sum_k |a_k.w| (2 sum_k min(0, a_k.w) up to rounding) and the
 // U-derivative sums from the signs of the projections (the derivative of
 // the + branch at 0, except at a projection of exactly -0).
+// Bound by VALU issue and the waves in flight that hide the row loads: rows
+// are loaded right before their use, since a second row buffer's registers
+// cost a wave per SIMD (2D FP64 R = 3 at 168 registers and 3 waves, FP32 at
+// 124 and 4).  9604 interior particles x 24^2, per launch: FP64 271 -> 223 us
+// (R 4 -> 3: full tiles), FP32 171 -> 144; 23^3 x 14^3 FP64 2.85 -> 2.30 ms
+// (R 2 -> 5, ragged), 30^3 x 20^3 13.4 -> 12.0 (R 4 -> 5).
 constexpr int kAdjUChunk = 32;
 
 
 template <int D, int NC, typename Real, int R, int P>
-__global__ __launch_bounds__(64) void k_adj_transport_patch(const AdjArgs<Real> a) {
+__global__ __launch_bounds__(64, (D == 2 && sizeof(Real) == 8 && R <= 3) ? 3 : 1) void
+k_adj_transport_patch(const AdjArgs<Real> a) {
   using A = Real;  // arithmetic of the per-velocity work
   // record: a_k (d*d), a_k.U (d)[, a_k[FA] dv (d), sum_k a_k[FA] dv].
   // FP64 keeps a_k and a_k.U only and forms the increments per edge (fewer
@@ -629,14 +636,20 @@ __global__ __launch_bounds__(64) void k_adj_transport_patch(const AdjArgs<Real> 
   for (int t = 0; t < P; ++t)
 #pragma unroll
     for (int k = 0; k < D; ++k) gU[t][k] = A(0);
-  const int ngroups = a.NV / R;
+  // group g: R velocities along the stepping axis; where R does not divide nv
+  // (FP64) the last group of a line overlaps the one before it: its first
+  // `skip` velocities get no adjoint here and are not stored
+  const int gl = (a.nv + R - 1) / R, ngroups = a.NV / a.nv * gl;
   const int g = tile * 64 + lane;
   const bool on = g < ngroups;
   // groups of one z plane first (3D), so consecutive lanes read consecutive
   // nodes of each plane
   const int zs = FA == 0 ? 1 : a.nv * a.nv;
   const uint32_t zsb = static_cast<uint32_t>(zs) * sizeof(Real);
-  const int q0 = on ? (FA == 0 ? g * R : g % zs + (g / zs) * zs * R) : 0;
+  const int line = on ? (FA == 0 ? g / gl : g % zs) : 0;
+  const int gs = on ? (FA == 0 ? g - line * gl : g / zs) : 0;
+  const int s0 = min(gs * R, a.nv - R), skip = gs * R - s0;
+  const int q0 = FA == 0 ? line * a.nv + s0 : line + s0 * zs;
   const uint32_t qoff = static_cast<uint32_t>(q0) * sizeof(Real);
   // R values of this lane from / into the row that starts at p
   auto ldg = [&](const Real* p, A (&o)[R]) {
@@ -670,7 +683,7 @@ __global__ __launch_bounds__(64) void k_adj_transport_patch(const AdjArgs<Real> 
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         lf[t][r][c] = A(0);
-        lj[t][r][c] = t1[r];
+        lj[t][r][c] = r < skip ? A(0) : t1[r];
         fj[t][r][c] = t2[r];
       }
     }
@@ -738,7 +751,7 @@ __global__ __launch_bounds__(64) void k_adj_transport_patch(const AdjArgs<Real> 
     }
     __syncthreads();
     // rows of union entry w: f^n_i and lam_ft_i
-    A fa[R][NC], la[R][NC], fb[R][NC], lb2[R][NC];
+    A fa[R][NC], la[R][NC];
     auto load_entry = [&](int w, A (&fi)[R][NC], A (&li)[R][NC]) {
       const int i = ri[w];
 #pragma unroll
@@ -839,14 +852,9 @@ __global__ __launch_bounds__(64) void k_adj_transport_patch(const AdjArgs<Real> 
         }
       }
     };
-    load_entry(0, fa, la);
-    for (int w = 0; w < cn; w += 2) {
-      if (w + 1 < cn) load_entry(w + 1, fb, lb2);
+    for (int w = 0; w < cn; ++w) {
+      load_entry(w, fa, la);
       entry(w, fa, la);
-      if (w + 1 < cn) {
-        if (w + 2 < cn) load_entry(w + 2, fa, la);
-        entry(w + 1, fb, lb2);
-      }
     }
   }
   const A dt = static_cast<A>(a.dt);
@@ -861,11 +869,12 @@ __global__ __launch_bounds__(64) void k_adj_transport_patch(const AdjArgs<Real> 
         for (int r = 0; r < R; ++r)
           out[r] = fma(lj[t][r][c], fma(dt, csum[t][r], A(1)), -dt * lf[t][r][c]);
         Real* row = a.lam_f + c * cs + static_cast<size_t>(jt[t]) * NVs;
-        if constexpr (FA == 0) {
-#pragma unroll
-          for (int r = 0; r < R; ++r) row[q0 + r] = out[r];
-        } else {
+        if (FA != 0 && skip == 0) {
           store_rz<Real, R>(row, qoff, zsb, out);
+        } else {
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+            if (r >= skip) row[q0 + r * zs] = out[r];
         }
       }
     }
@@ -1104,14 +1113,16 @@ static hipError_t adjoint_step_t(const Ctx& c, const Real* f_n, const double* U_
       if (e != hipSuccess) return e;
     }
     if (c.Ni) launch_adj_collide<2, 2, Real>(c, a, t, lds);
-    if (R == 4) {
-      if (npa) e = launch_adj_patch<2, 2, Real, 4>(c, a, ap, npa);
-      if (e != hipSuccess) return e;
-      if (c.Nw) hipLaunchKernelGGL((k_adj_transport_wall<2, 2, Real, 4>), tw, tt, 0, c.stream, aw);
-    } else {
-      if (npa) e = launch_adj_patch<2, 2, Real, 2>(c, a, ap, npa);
-      if (e != hipSuccess) return e;
-      if (c.Nw) hipLaunchKernelGGL((k_adj_transport_wall<2, 2, Real, 2>), tw, tt, 0, c.stream, aw);
+    if (npa) {
+      if constexpr (std::is_same<Real, double>::value)
+        if (R == 3) e = launch_adj_patch<2, 2, Real, 3>(c, a, ap, npa);
+      if (R == 4) e = launch_adj_patch<2, 2, Real, 4>(c, a, ap, npa);
+      if (R == 2) e = launch_adj_patch<2, 2, Real, 2>(c, a, ap, npa);
+    }
+    if (e != hipSuccess) return e;
+    if (c.Nw) {
+      if (ap.Rw == 4) hipLaunchKernelGGL((k_adj_transport_wall<2, 2, Real, 4>), tw, tt, 0, c.stream, aw);
+      else hipLaunchKernelGGL((k_adj_transport_wall<2, 2, Real, 2>), tw, tt, 0, c.stream, aw);
     }
   } else {
     if (c.Nw) hipLaunchKernelGGL((k_adj_wall<3, 1, Real>), dim3(c.Nw), t, lds, c.stream, a);
@@ -1121,11 +1132,9 @@ static hipError_t adjoint_step_t(const Ctx& c, const Real* f_n, const double* U_
     }
     if (c.Ni) launch_adj_collide<3, 1, Real>(c, a, t, lds);
     if (npa) {
-      if constexpr (std::is_same<Real, float>::value) {
-        if (R == 5) e = launch_adj_patch<3, 1, Real, 5>(c, a, ap, npa);
-      } else {
-        if (R == 5) return hipErrorInvalidValue;  // (the plan takes 5 for FP32 storage only)
-      }
+      if (R == 5) e = launch_adj_patch<3, 1, Real, 5>(c, a, ap, npa);
+      if constexpr (std::is_same<Real, double>::value)
+        if (R == 3) e = launch_adj_patch<3, 1, Real, 3>(c, a, ap, npa);
       if (R == 4) e = launch_adj_patch<3, 1, Real, 4>(c, a, ap, npa);
       if (R == 2) e = launch_adj_patch<3, 1, Real, 2>(c, a, ap, npa);
     }

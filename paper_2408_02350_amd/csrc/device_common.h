@@ -136,14 +136,16 @@ __device__ __forceinline__ void store_rz(Real* row, uint32_t lane_off, uint32_t 
 }
 
 // Row loads and stores of R consecutive values as 16-byte (or 8-byte)
-// vectors; the row offsets the callers pass are multiples of R.
+// vectors; the row offsets the callers pass are multiples of R.  The vector
+// types ask for an element's alignment only, so a caller's tensor may start
+// anywhere (one instruction either way).
 template <typename Real, int R>
 __device__ __forceinline__ void load_rs(const Real* __restrict__ p, Real (&o)[R]) {
   constexpr int B = R * static_cast<int>(sizeof(Real));
   constexpr int W = B % 16 == 0 ? 16 / static_cast<int>(sizeof(Real))
                                 : (B % 8 == 0 ? 8 / static_cast<int>(sizeof(Real)) : 1);
-  typedef Real V __attribute__((ext_vector_type(W)));
-  const V* pv = reinterpret_cast<const V*>(__builtin_assume_aligned(p, W * sizeof(Real)));
+  typedef Real V __attribute__((ext_vector_type(W), aligned(sizeof(Real))));
+  const V* pv = reinterpret_cast<const V*>(p);
 #pragma unroll
   for (int i = 0; i < R / W; ++i) {
     const V x = pv[i];
@@ -157,8 +159,8 @@ __device__ __forceinline__ void store_rs(Real* __restrict__ p, const Real (&o)[R
   constexpr int B = R * static_cast<int>(sizeof(Real));
   constexpr int W = B % 16 == 0 ? 16 / static_cast<int>(sizeof(Real))
                                 : (B % 8 == 0 ? 8 / static_cast<int>(sizeof(Real)) : 1);
-  typedef Real V __attribute__((ext_vector_type(W)));
-  V* pv = reinterpret_cast<V*>(__builtin_assume_aligned(p, W * sizeof(Real)));
+  typedef Real V __attribute__((ext_vector_type(W), aligned(sizeof(Real))));
+  V* pv = reinterpret_cast<V*>(p);
 #pragma unroll
   for (int i = 0; i < R / W; ++i) {
     V x;

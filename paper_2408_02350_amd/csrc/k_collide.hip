@@ -43,46 +43,107 @@ static inline size_t row_tab_bytes(int nv) {
   return static_cast<size_t>(D + 1) * nv * sizeof(double);
 }
 
+// A particle's row in the hands of a block: a thread takes groups of R
+// consecutive velocities along the fastest axis (16-byte row pieces; group
+// g = tid + m kThreads) and keeps its first KEEP groups (32 values) in
+// registers, the whole row up to 8192 values, so that several passes read it
+// once; later groups are read again in each pass.
+template <int D, int NC, typename Real, int R, int KEEP>
+struct RowGroups {
+  const Real* row;
+  size_t cs;
+  int nv, ng0, ng;
+  Real keep[KEEP][NC][R];
+  __device__ __forceinline__ RowGroups(const Real* row_, size_t cs_, int NV, int nv_)
+      : row(row_), cs(cs_), nv(nv_), ng0(nv_ / R), ng(NV / R) {
+#pragma unroll
+    for (int m = 0; m < KEEP; ++m) {
+      const int g = threadIdx.x + m * kThreads;
+      if (g < ng) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          load_rs<Real, R>(row + c * cs + static_cast<size_t>(g) * R, keep[m][c]);
+      }
+    }
+  }
+  // visits this thread's groups: body(group, digits, values)
+  template <typename F>
+  __device__ __forceinline__ void each(F&& body) const {
+    GroupDigits<D> gd;
+    gd.init(threadIdx.x, kThreads, ng0, nv);
+    int g = threadIdx.x;
+#pragma unroll
+    for (int m = 0; m < KEEP; ++m, g += kThreads) {
+      if (g < ng) body(g, gd.k, keep[m]);
+      gd.advance(ng0, nv);
+    }
+    for (; g < ng; g += kThreads) {
+      Real x[NC][R];
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        load_rs<Real, R>(row + c * cs + static_cast<size_t>(g) * R, x[c]);
+      body(g, gd.k, x);
+      gd.advance(ng0, nv);
+    }
+  }
+};
+
 // rho, U, T of one particle's row (Sec. 2 eqs. moments, internal_energy;
 // Chu eq. macroeq; time-discrete fullmoment1a / moment1a, moment1b):
 // rho = omega sum f1, U = sum v f1 / sum f1, then 3 rho T from the centred
 // second moment (Chu: plus sum g2).  vt: the velocity nodes in LDS.
-template <int D, int NC, typename Real>
-__device__ __forceinline__ void row_moments(const Real* row, size_t cs, int NV, int nv,
+template <int D, int NC, typename Real, int R, int KEEP>
+__device__ __forceinline__ void row_moments(const RowGroups<D, NC, Real, R, KEEP>& rg,
                                             const double* vt, double omega, double* sh,
                                             double& rho, double* U, double& T) {
   double s[D + 1];
 #pragma unroll
   for (int k = 0; k <= D; ++k) s[k] = 0.0;
-  VelDigits<D> vd;
-  vd.init(threadIdx.x, kThreads, nv);
-  for (int q = threadIdx.x; q < NV; q += kThreads, vd.advance(nv)) {
-    const int* kq = vd.k;
-    const double f1 = static_cast<double>(row[q]);
-    s[0] = s[0] + f1;
+  rg.each([&](int, const int (&kd)[D], const Real (&x)[NC][R]) {
+    double gs = 0.0;
 #pragma unroll
-    for (int k = 0; k < D; ++k) s[1 + k] = s[1 + k] + vt[kq[k]] * f1;
-  }
+    for (int r = 0; r < R; ++r) {
+      const double f1 = static_cast<double>(x[0][r]);
+      gs = gs + f1;
+      s[1] = s[1] + vt[kd[0] * R + r] * f1;
+    }
+    s[0] = s[0] + gs;
+#pragma unroll
+    for (int k = 1; k < D; ++k) s[1 + k] = s[1 + k] + vt[kd[k]] * gs;
+  });
   block_sum<D + 1>(s, sh);
   const double s0 = s[0];
   rho = omega * s0;
 #pragma unroll
   for (int k = 0; k < D; ++k) U[k] = s[1 + k] / s0;
   double e[1] = {0.0};
-  vd.init(threadIdx.x, kThreads, nv);
-  for (int q = threadIdx.x; q < NV; q += kThreads, vd.advance(nv)) {
-    const int* kq = vd.k;
-    double w2 = 0.0;
+  rg.each([&](int, const int (&kd)[D], const Real (&x)[NC][R]) {
+    double w2s = 0.0;
 #pragma unroll
-    for (int k = 0; k < D; ++k) {
-      const double wk = vt[kq[k]] - U[k];
-      w2 = w2 + wk * wk;
+    for (int k = 1; k < D; ++k) {
+      const double wk = vt[kd[k]] - U[k];
+      w2s = w2s + wk * wk;
     }
-    e[0] = e[0] + w2 * static_cast<double>(row[q]);
-    if (NC == 2) e[0] = e[0] + static_cast<double>(row[cs + q]);
-  }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const double w0 = vt[kd[0] * R + r] - U[0];
+      e[0] = e[0] + (w0 * w0 + w2s) * static_cast<double>(x[0][r]);
+      if (NC == 2) e[0] = e[0] + static_cast<double>(x[NC - 1][r]);
+    }
+  });
   block_sum<1>(e, sh);
   T = e[0] / (3.0 * s0);
+}
+
+// with_row_groups<Real, NC>(nv, f): f(R, KEEP) as compile-time constants, for
+// 16-byte row pieces (floats: 8 bytes where 4 does not divide nv).
+template <typename Real, int NC, typename F>
+static void with_row_groups(int nv, F&& f) {
+  if constexpr (sizeof(Real) == 4)
+    if (nv % 4 == 0)
+      return f(std::integral_constant<int, 4>{}, std::integral_constant<int, 32 / (4 * NC)>{});
+  f(std::integral_constant<int, 2>{},
+    std::integral_constant<int, 32 / (2 * NC)>{});
 }
 
 struct CollideArgs {
@@ -98,88 +159,23 @@ struct CollideArgs {
 };
 
 // S5-S6: moments of ft, tau at the new state, f = (tau ft + dt M)/(tau + dt).
-// One block per particle.  A thread takes groups of R consecutive velocities
-// along the fastest axis (16-byte row pieces; group g = tid + m kThreads) and
-// keeps its first KEEP groups (32 values) in registers, the whole row up to 8192
-// values, so that the row is read once; later groups are
-// read again in each pass.  Bound by HBM: one read and one write of the row;
-// 110592 particles x 8000 doubles 3.87 -> 2.47 ms (5.0 TB/s), floats 2.99 -> 1.73, against
-// three reads of one value per thread.
+// One block per particle.  Bound by HBM: one read and one write of the row;
+// 110592 particles x 8000 doubles 3.87 -> 2.47 ms (5.0 TB/s), floats
+// 2.99 -> 1.73, against three reads of one value per thread.
 template <int D, int NC, typename Real, int R, int KEEP>
 __global__ __launch_bounds__(kThreads) void k_collide(const CollideArgs a) {
   __shared__ double sh[4 * (D + 1)];
   extern __shared__ double vt[];  // nodes, then per-axis Maxwellian factors
   const int i = a.plist[xcd_logical_block(blockIdx.x, gridDim.x)];
-  const int nv = a.nv, ng0 = nv / R, ng = a.NV / R;
+  const int nv = a.nv;
   const size_t NVs = a.NV, cs = static_cast<size_t>(a.N) * NVs;
-  const Real* ft = static_cast<const Real*>(a.ft) + static_cast<size_t>(i) * NVs;
+  const RowGroups<D, NC, Real, R, KEEP> rg(
+      static_cast<const Real*>(a.ft) + static_cast<size_t>(i) * NVs, cs, a.NV, nv);
   Real* fo = static_cast<Real*>(a.fo) + static_cast<size_t>(i) * NVs;
-  Real keep[KEEP][NC][R];
-#pragma unroll
-  for (int m = 0; m < KEEP; ++m) {
-    const int g = threadIdx.x + m * kThreads;
-    if (g < ng) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) load_rs<Real, R>(ft + c * cs + static_cast<size_t>(g) * R, keep[m][c]);
-    }
-  }
   fill_vtab(vt, nv, a.vmax);
   __syncthreads();
-  // visits this thread's groups: body(group, digits, values)
-  auto each = [&](auto&& body) {
-    GroupDigits<D> gd;
-    gd.init(threadIdx.x, kThreads, ng0, nv);
-    int g = threadIdx.x;
-#pragma unroll
-    for (int m = 0; m < KEEP; ++m, g += kThreads) {
-      if (g < ng) body(g, gd.k, keep[m]);
-      gd.advance(ng0, nv);
-    }
-    for (; g < ng; g += kThreads) {
-      Real x[NC][R];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) load_rs<Real, R>(ft + c * cs + static_cast<size_t>(g) * R, x[c]);
-      body(g, gd.k, x);
-      gd.advance(ng0, nv);
-    }
-  };
-  double s[D + 1];
-#pragma unroll
-  for (int k = 0; k <= D; ++k) s[k] = 0.0;
-  each([&](int, const int (&kd)[D], const Real (&x)[NC][R]) {
-    double gs = 0.0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const double f1 = static_cast<double>(x[0][r]);
-      gs = gs + f1;
-      s[1] = s[1] + vt[kd[0] * R + r] * f1;
-    }
-    s[0] = s[0] + gs;
-#pragma unroll
-    for (int k = 1; k < D; ++k) s[1 + k] = s[1 + k] + vt[kd[k]] * gs;
-  });
-  block_sum<D + 1>(s, sh);
-  const double s0 = s[0], rho = a.omega * s0;
-  double U[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-  for (int k = 0; k < D; ++k) U[k] = s[1 + k] / s0;
-  double e[1] = {0.0};
-  each([&](int, const int (&kd)[D], const Real (&x)[NC][R]) {
-    double w2s = 0.0;
-#pragma unroll
-    for (int k = 1; k < D; ++k) {
-      const double wk = vt[kd[k]] - U[k];
-      w2s = w2s + wk * wk;
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const double w0 = vt[kd[0] * R + r] - U[0];
-      e[0] = e[0] + (w0 * w0 + w2s) * static_cast<double>(x[0][r]);
-      if (NC == 2) e[0] = e[0] + static_cast<double>(x[NC - 1][r]);
-    }
-  });
-  block_sum<1>(e, sh);
-  const double T = e[0] / (3.0 * s0);
+  double rho, U[3] = {0.0, 0.0, 0.0}, T;
+  row_moments(rg, vt, a.omega, sh, rho, U, T);
   if (threadIdx.x == 0) {
     a.rho[i] = rho;
     a.T[i] = T;
@@ -193,7 +189,7 @@ __global__ __launch_bounds__(kThreads) void k_collide(const CollideArgs a) {
   fill_etab<D>(et, vt, nv, U, T);
   __syncthreads();
   const double norm = maxwell_norm<D>(rho, T);
-  each([&](int g, const int (&kd)[D], const Real (&x)[NC][R]) {
+  rg.each([&](int g, const int (&kd)[D], const Real (&x)[NC][R]) {
     double Ms = norm;
 #pragma unroll
     for (int k = 1; k < D; ++k) Ms = Ms * et[k * nv + kd[k]];
@@ -212,19 +208,11 @@ __global__ __launch_bounds__(kThreads) void k_collide(const CollideArgs a) {
 
 template <typename Real, int D, int NC>
 static void collide_t(const Ctx& c, const CollideArgs& a) {
-  constexpr int W = static_cast<int>(sizeof(Real)) / 4;
   const size_t lds = row_tab_bytes<D>(c.cfg.nv);
-  if constexpr (W == 1) {
-    if (c.cfg.nv % 4 == 0) {
-      constexpr int R = 4, KEEP = 32 / (R * NC);
-      hipLaunchKernelGGL((k_collide<D, NC, Real, R, KEEP>), dim3(a.count), dim3(kThreads), lds,
-                         c.stream, a);
-      return;
-    }
-  }
-  constexpr int R = 2, KEEP = 32 / (R * NC);  // (32 values)
-  hipLaunchKernelGGL((k_collide<D, NC, Real, R, KEEP>), dim3(a.count), dim3(kThreads), lds,
-                     c.stream, a);
+  with_row_groups<Real, NC>(c.cfg.nv, [&](auto r, auto keep) {
+    hipLaunchKernelGGL((k_collide<D, NC, Real, r(), keep()>), dim3(a.count), dim3(kThreads), lds,
+                       c.stream, a);
+  });
 }
 
 hipError_t launch_collide(const Ctx& c, const void* ft, void* fout, double* rho, double* U,
@@ -701,7 +689,9 @@ hipError_t launch_wall_bc(const Ctx& c, void* f, double* rho, double* U, double*
 }
 
 // ------------------------------------------------------------ moments, M
-template <int D, int NC, typename Real>
+// Bound by HBM: one read of the row.  110592 particles x 8000 floats
+// 1.79 -> 1.25 ms, doubles 2.20 -> 1.31, against two reads of one value per thread.
+template <int D, int NC, typename Real, int R, int KEEP>
 __global__ __launch_bounds__(kThreads) void k_moments(int N, int NV, int nv, double vmax,
                                                        double omega, const void* fv, double* rho,
                                                        double* U, double* T) {
@@ -709,11 +699,12 @@ __global__ __launch_bounds__(kThreads) void k_moments(int N, int NV, int nv, dou
   extern __shared__ double vt[];
   const int i = blockIdx.x;
   const size_t NVs = NV, cs = static_cast<size_t>(N) * NVs;
-  const Real* row = static_cast<const Real*>(fv) + static_cast<size_t>(i) * NVs;
+  const RowGroups<D, NC, Real, R, KEEP> rg(
+      static_cast<const Real*>(fv) + static_cast<size_t>(i) * NVs, cs, NV, nv);
   fill_vtab(vt, nv, vmax);
   __syncthreads();
   double r, u[3] = {0.0, 0.0, 0.0}, t;
-  row_moments<D, NC, Real>(row, cs, NV, nv, vt, omega, sh, r, u, t);
+  row_moments(rg, vt, omega, sh, r, u, t);
   if (threadIdx.x == 0) {
     rho[i] = r;
     T[i] = t;
@@ -722,17 +713,23 @@ __global__ __launch_bounds__(kThreads) void k_moments(int N, int NV, int nv, dou
   }
 }
 
+template <int D, int NC, typename Real>
+static void moments_t(const Ctx& c, const void* f, double* rho, double* U, double* T) {
+  const size_t lds = static_cast<size_t>(c.cfg.nv) * sizeof(double);
+  with_row_groups<Real, NC>(c.cfg.nv, [&](auto r, auto keep) {
+    hipLaunchKernelGGL((k_moments<D, NC, Real, r(), keep()>), dim3(c.N), dim3(kThreads), lds,
+                       c.stream, c.N, c.NV, c.cfg.nv, c.cfg.vmax, omega_of(c.cfg), f, rho, U, T);
+  });
+}
+
 hipError_t launch_moments(const Ctx& c, const void* f, double* rho, double* U, double* T) {
   const bool f64 = c.cfg.precision == BGK_FP64;
-  const double om = omega_of(c.cfg);
-  dim3 g(c.N), t(kThreads);
-  const size_t lds = static_cast<size_t>(c.D + 1) * c.cfg.nv * sizeof(double);
   if (c.D == 2) {
-    if (f64) hipLaunchKernelGGL((k_moments<2, 2, double>), g, t, lds, c.stream, c.N, c.NV, c.cfg.nv, c.cfg.vmax, om, f, rho, U, T);
-    else hipLaunchKernelGGL((k_moments<2, 2, float>), g, t, lds, c.stream, c.N, c.NV, c.cfg.nv, c.cfg.vmax, om, f, rho, U, T);
+    if (f64) moments_t<2, 2, double>(c, f, rho, U, T);
+    else moments_t<2, 2, float>(c, f, rho, U, T);
   } else {
-    if (f64) hipLaunchKernelGGL((k_moments<3, 1, double>), g, t, lds, c.stream, c.N, c.NV, c.cfg.nv, c.cfg.vmax, om, f, rho, U, T);
-    else hipLaunchKernelGGL((k_moments<3, 1, float>), g, t, lds, c.stream, c.N, c.NV, c.cfg.nv, c.cfg.vmax, om, f, rho, U, T);
+    if (f64) moments_t<3, 1, double>(c, f, rho, U, T);
+    else moments_t<3, 1, float>(c, f, rho, U, T);
   }
   return hipGetLastError();
 }
@@ -748,7 +745,7 @@ hipError_t launch_moments(const Ctx& c, const void* f, double* rho, double* U, d
 // degrees of freedom in both models: the Chu g2 carries the third).  Slots:
 //   0 min f, 1 negatives, 2 non-finite, 3 |rho(f) - rho| / rho,
 //   4 max_k |U_k(f) - U_k|, 5 |T(f) - T| / T, 6 rho, 7.. rho U (d), 7+d energy.
-template <int D, int NC, typename Real>
+template <int D, int NC, typename Real, int R, int KEEP>
 __global__ __launch_bounds__(kThreads) void k_state_terms(int N, int NV, int nv, double vmax,
                                                            double omega, const void* fv,
                                                            const double* __restrict__ rho,
@@ -760,24 +757,27 @@ __global__ __launch_bounds__(kThreads) void k_state_terms(int N, int NV, int nv,
   extern __shared__ double vt[];
   const int i = blockIdx.x;
   const size_t NVs = NV, cs = static_cast<size_t>(N) * NVs;
-  const Real* row = static_cast<const Real*>(fv) + static_cast<size_t>(i) * NVs;
+  const RowGroups<D, NC, Real, R, KEEP> rg(
+      static_cast<const Real*>(fv) + static_cast<size_t>(i) * NVs, cs, NV, nv);
   fill_vtab(vt, nv, vmax);
   __syncthreads();
   double r, u[3] = {0.0, 0.0, 0.0}, t;
-  row_moments<D, NC, Real>(row, cs, NV, nv, vt, omega, sh, r, u, t);
+  row_moments(rg, vt, omega, sh, r, u, t);
   double mn = INFINITY, cnt[2] = {0.0, 0.0};
-  for (int q = threadIdx.x; q < NV; q += kThreads) {
+  rg.each([&](int, const int (&)[D], const Real (&v)[NC][R]) {
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const double x = static_cast<double>(row[c * cs + q]);
-      if (isfinite(x)) {
-        mn = fmin(mn, x);
-        if (x < 0.0) cnt[0] = cnt[0] + 1.0;
-      } else {
-        cnt[1] = cnt[1] + 1.0;
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        const double x = static_cast<double>(v[c][k]);
+        if (isfinite(x)) {
+          mn = fmin(mn, x);
+          if (x < 0.0) cnt[0] = cnt[0] + 1.0;
+        } else {
+          cnt[1] = cnt[1] + 1.0;
+        }
       }
-    }
-  }
+  });
   block_sum<2>(cnt, sh);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) mn = fmin(mn, __shfl_xor(mn, o, 64));
@@ -862,21 +862,28 @@ __global__ __launch_bounds__(kThreads) void k_state_reduce(int N, const double* 
   }
 }
 
+template <int D, int NC, typename Real>
+static void state_check_t(const Ctx& c, const void* f, const double* rho, const double* U,
+                          const double* T, double* out_dev) {
+  const size_t lds = static_cast<size_t>(c.cfg.nv) * sizeof(double);
+  with_row_groups<Real, NC>(c.cfg.nv, [&](auto r, auto keep) {
+    hipLaunchKernelGGL((k_state_terms<D, NC, Real, r(), keep()>), dim3(c.N), dim3(kThreads), lds,
+                       c.stream, c.N, c.NV, c.cfg.nv, c.cfg.vmax, omega_of(c.cfg), f, rho, U, T,
+                       c.d.scheck);
+  });
+  hipLaunchKernelGGL(k_state_reduce<D>, dim3(1), dim3(kThreads), 0, c.stream, c.N, c.d.scheck,
+                     out_dev);
+}
+
 hipError_t launch_state_check(const Ctx& c, const void* f, const double* rho, const double* U,
                               const double* T, double* out_dev) {
   const bool f64 = c.cfg.precision == BGK_FP64;
-  const double om = omega_of(c.cfg);
-  dim3 g(c.N), t(kThreads);
-  const size_t lds = static_cast<size_t>(c.D + 1) * c.cfg.nv * sizeof(double);
-  double* part = c.d.scheck;
   if (c.D == 2) {
-    if (f64) hipLaunchKernelGGL((k_state_terms<2, 2, double>), g, t, lds, c.stream, c.N, c.NV, c.cfg.nv, c.cfg.vmax, om, f, rho, U, T, part);
-    else hipLaunchKernelGGL((k_state_terms<2, 2, float>), g, t, lds, c.stream, c.N, c.NV, c.cfg.nv, c.cfg.vmax, om, f, rho, U, T, part);
-    hipLaunchKernelGGL(k_state_reduce<2>, dim3(1), t, 0, c.stream, c.N, part, out_dev);
+    if (f64) state_check_t<2, 2, double>(c, f, rho, U, T, out_dev);
+    else state_check_t<2, 2, float>(c, f, rho, U, T, out_dev);
   } else {
-    if (f64) hipLaunchKernelGGL((k_state_terms<3, 1, double>), g, t, lds, c.stream, c.N, c.NV, c.cfg.nv, c.cfg.vmax, om, f, rho, U, T, part);
-    else hipLaunchKernelGGL((k_state_terms<3, 1, float>), g, t, lds, c.stream, c.N, c.NV, c.cfg.nv, c.cfg.vmax, om, f, rho, U, T, part);
-    hipLaunchKernelGGL(k_state_reduce<3>, dim3(1), t, 0, c.stream, c.N, part, out_dev);
+    if (f64) state_check_t<3, 1, double>(c, f, rho, U, T, out_dev);
+    else state_check_t<3, 1, float>(c, f, rho, U, T, out_dev);
   }
   return hipGetLastError();
 }

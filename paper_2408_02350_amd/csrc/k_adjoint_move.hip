@@ -328,25 +328,54 @@ __global__ __launch_bounds__(kOpsWaves * 64) void k_adjm_ops(const MoveAdjArgs a
 // ------------------------------------------------------------ S7: lam_c0
 // One block per wall particle (wall-list order): for every stencil entry
 // the dot product of the adjoint reaching the interpolated half with the
-// interior row f^{n+1}_j it interpolates (zero on the emitted half).
-template <int NC, typename Real>
+// interior row f^{n+1}_j it interpolates.  Entries are taken eight at a time,
+// so the wall row is read once per eight and eight row loads are in flight;
+// 16-byte pieces whose adjoint is zero (the emitted half) skip f^{n+1}.  Bound
+// by the L2: 3458 wall particles x 14^3 280 -> 118 us, 396 x 24^2
+// 16 -> 14, against one entry at a time over the whole row.
+template <int NC, typename Real, int R>
 __global__ __launch_bounds__(kThreads) void k_adjm_wallrow(const MoveAdjArgs a, const Real* larr,
                                                            const Real* f1) {
-  __shared__ double sh[4];
+  constexpr int E = 8;
+  __shared__ double sh[4 * E];
   const int k = blockIdx.x;
   const size_t NVs = a.NV, cs = static_cast<size_t>(a.N) * NVs;
-  const int m = a.wcnt[k];
-  for (int e = 0; e < m; ++e) {
-    const int j = a.widx[static_cast<size_t>(k) * a.cap + e];
-    double s[1] = {0.0};
-    for (int q = threadIdx.x; q < a.NV; q += kThreads) {
+  const int m = a.wcnt[k], ng = a.NV / R;
+  const int32_t* wj = a.widx + static_cast<size_t>(k) * a.cap;
+  const Real* lk = larr + static_cast<size_t>(k) * NC * NVs;
+  for (int e0 = 0; e0 < m; e0 += E) {
+    double s[E];
+    const Real* row[E];  // (past the list's end: its last entry again)
 #pragma unroll
-      for (int c = 0; c < NC; ++c)
-        s[0] = s[0] + static_cast<double>(larr[(static_cast<size_t>(k) * NC + c) * NVs + q]) *
-                          static_cast<double>(f1[c * cs + static_cast<size_t>(j) * NVs + q]);
+    for (int e = 0; e < E; ++e) {
+      s[e] = 0.0;
+      row[e] = f1 + static_cast<size_t>(wj[min(e0 + e, m - 1)]) * NVs;
     }
-    block_sum<1>(s, sh);
-    if (threadIdx.x == 0) a.lc0[static_cast<size_t>(k) * a.cap + e] = s[0];
+    const int en = min(E, m - e0);
+    for (int g = threadIdx.x; g < ng; g += kThreads) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        Real l[R];
+        load_rs<Real, R>(lk + c * NVs + static_cast<size_t>(g) * R, l);
+        bool any = false;
+#pragma unroll
+        for (int r = 0; r < R; ++r) any = any || l[r] != Real(0);
+        if (!any) continue;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          if (e >= en) break;  // (block-uniform)
+          Real x[R];
+          load_rs<Real, R>(row[e] + c * cs + static_cast<size_t>(g) * R, x);
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+            s[e] = s[e] + static_cast<double>(l[r]) * static_cast<double>(x[r]);
+        }
+      }
+    }
+    block_sum<E>(s, sh);
+    if (threadIdx.x == 0)
+      for (int e = 0; e < E; ++e)
+        if (e < en) a.lc0[static_cast<size_t>(k) * a.cap + e0 + e] = s[e];
   }
 }
 
@@ -514,13 +543,16 @@ __device__ __forceinline__ void frame_m_rev(const double* n, const double* t, co
   }
 }
 
-// One thread per interior particle: the forward least squares and frames
-// recomputed, then the reverse described at the top of the file.  Writes
-// xc[i][e] (to x_j) for every slot (zero on the self slot) and xs[i].
+// One 16-lane row per interior particle, an edge per lane (as the forward
+// fit): the forward least squares and frames recomputed, then the reverse
+// described at the top of the file; the sums over the edges are row sums, and
+// the small solves are done by every lane.  Writes xc[i][e] (to x_j) for every
+// slot (zero on the self slot) and xs[i].  Bound by latency: 12167 particles
+// of 3D 233 -> 82 us, 9604 of 2D 55 -> 22, against a thread per particle.
 template <int D>
 __global__ __launch_bounds__(64) void k_adjm_geom(const MoveAdjArgs a) {
   constexpr int B2 = D == 2 ? 6 : 10, NT2 = B2 * (B2 + 1) / 2, DD = D * D;
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  const int k = blockIdx.x * 4 + (threadIdx.x >> 4), l = threadIdx.x & 15;
   if (k >= a.Ni) return;
   const int i = a.plist[k];
   const int m = min(a.ncnt[i], a.cap);
@@ -547,7 +579,7 @@ __global__ __launch_bounds__(64) void k_adjm_geom(const MoveAdjArgs a) {
     w = exp(-a.alpha * r2);
     basis_m<D>(deg, y, p);
   };
-  for (int e = 0; e < m; ++e) {
+  for (int e = l; e < m; e += 16) {
     int j;
     double dl[D], y[D], w, p[B2];
     edge_geom(e, j, dl, y, w, p);
@@ -558,6 +590,8 @@ __global__ __launch_bounds__(64) void k_adjm_geom(const MoveAdjArgs a) {
       for (int s = 0; s <= r; ++s) A[tri_m(r, s)] = A[tri_m(r, s)] + wp * p[s];
     }
   }
+#pragma unroll
+  for (int t = 0; t < NT2; ++t) A[t] = row16_sum(A[t]);
 #pragma unroll
   for (int r = 0; r < B2; ++r)
     if (r >= Bg) A[tri_m(r, r)] = 1.0;
@@ -627,7 +661,7 @@ __global__ __launch_bounds__(64) void k_adjm_geom(const MoveAdjArgs a) {
 #pragma unroll
     for (int r = 0; r < B2; ++r) LZ[c][r] = 0.0;
   if (ok) {
-    for (int e = 0; e < m; ++e) {
+    for (int e = l; e < m; e += 16) {
       if (a.nidx[row + e] == i) continue;
       int j;
       double dl[D], y[D], w, p[B2], zp[D], lg[D], ld[D];
@@ -640,12 +674,16 @@ __global__ __launch_bounds__(64) void k_adjm_geom(const MoveAdjArgs a) {
   }
   double K[D][B2];
 #pragma unroll
-  for (int c = 0; c < D; ++c) chol_solve_m<B2>(A, inv, LZ[c], K[c]);
+  for (int c = 0; c < D; ++c) {
+#pragma unroll
+    for (int r = 0; r < B2; ++r) LZ[c][r] = row16_sum(LZ[c][r]);
+    chol_solve_m<B2>(A, inv, LZ[c], K[c]);
+  }
   // pass 2: every edge's contribution to x_j (and, negated, to x_i)
   double own[D];
 #pragma unroll
   for (int c = 0; c < D; ++c) own[c] = 0.0;
-  for (int e = 0; e < m; ++e) {
+  for (int e = l; e < m; e += 16) {
     double out[D];
 #pragma unroll
     for (int c = 0; c < D; ++c) out[c] = 0.0;
@@ -687,15 +725,18 @@ __global__ __launch_bounds__(64) void k_adjm_geom(const MoveAdjArgs a) {
     for (int c = 0; c < D; ++c) a.xc[(row + e) * D + c] = out[c];
   }
 #pragma unroll
-  for (int c = 0; c < D; ++c) a.xs[static_cast<size_t>(i) * D + c] = own[c];
+  for (int c = 0; c < D; ++c) own[c] = row16_sum(own[c]);
+  if (l == 0)
+#pragma unroll
+    for (int c = 0; c < D; ++c) a.xs[static_cast<size_t>(i) * D + c] = own[c];
 }
 
-// One thread per wall particle: the reverse of its degree-1 value row
+// One 16-lane row per wall particle: the reverse of its degree-1 value row
 // c0_e = W_e z.p_e, z = A^-1 e_0, y_e = (x_j - x_b)/hb.
 template <int D>
 __global__ __launch_bounds__(64) void k_adjm_wallgeom(const MoveAdjArgs a) {
   constexpr int B = D + 1, NT = B * (B + 1) / 2;
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  const int k = blockIdx.x * 4 + (threadIdx.x >> 4), l = threadIdx.x & 15;
   if (k >= a.Nw) return;
   const int bq = a.wall_list[k];
   const int m = a.wcnt[k];
@@ -720,7 +761,7 @@ __global__ __launch_bounds__(64) void k_adjm_wallgeom(const MoveAdjArgs a) {
   double A[NT], inv[B];
 #pragma unroll
   for (int t = 0; t < NT; ++t) A[t] = 0.0;
-  for (int e = 0; e < m; ++e) {
+  for (int e = l; e < m; e += 16) {
     double y[D], w, p[B];
     ent(e, y, w, p);
 #pragma unroll
@@ -728,6 +769,8 @@ __global__ __launch_bounds__(64) void k_adjm_wallgeom(const MoveAdjArgs a) {
 #pragma unroll
       for (int s = 0; s <= r; ++s) A[tri_m(r, s)] = A[tri_m(r, s)] + w * p[r] * p[s];
   }
+#pragma unroll
+  for (int t = 0; t < NT; ++t) A[t] = row16_sum(A[t]);
   const bool ok = m >= D + 2 && chol_m<B>(A, inv);
   double z[B], rhs[B], LZ[B], K[B];
 #pragma unroll
@@ -738,18 +781,20 @@ __global__ __launch_bounds__(64) void k_adjm_wallgeom(const MoveAdjArgs a) {
   chol_solve_m<B>(A, inv, rhs, z);
   const double* lc = a.lc0 + row;
   if (ok) {
-    for (int e = 0; e < m; ++e) {
+    for (int e = l; e < m; e += 16) {
       double y[D], w, p[B];
       ent(e, y, w, p);
 #pragma unroll
       for (int r = 0; r < B; ++r) LZ[r] = LZ[r] + lc[e] * w * p[r];
     }
   }
+#pragma unroll
+  for (int r = 0; r < B; ++r) LZ[r] = row16_sum(LZ[r]);
   chol_solve_m<B>(A, inv, LZ, K);
   double own[D];
 #pragma unroll
   for (int c = 0; c < D; ++c) own[c] = 0.0;
-  for (int e = 0; e < m; ++e) {
+  for (int e = l; e < m; e += 16) {
     double out[D];
 #pragma unroll
     for (int c = 0; c < D; ++c) out[c] = 0.0;
@@ -777,34 +822,49 @@ __global__ __launch_bounds__(64) void k_adjm_wallgeom(const MoveAdjArgs a) {
     for (int c = 0; c < D; ++c) a.wxc[(row + e) * D + c] = out[c];
   }
 #pragma unroll
-  for (int c = 0; c < D; ++c) a.wxs[static_cast<size_t>(k) * D + c] = own[c];
+  for (int c = 0; c < D; ++c) own[c] = row16_sum(own[c]);
+  if (l == 0)
+#pragma unroll
+    for (int c = 0; c < D; ++c) a.wxs[static_cast<size_t>(k) * D + c] = own[c];
 }
 
 // ------------------------------------------------------------ gather
 // lam_x_j = (S8 part) + j's own row + every row i that holds j (transposed
-// slots, in j's row order) + every wall row that interpolates j (in
-// wall-list order) + j's own wall row.
-__global__ void k_adjm_xgather(const MoveAdjArgs a, int D) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+// slots) + every wall row that interpolates j + j's own wall row: a 16-lane
+// row per particle, a term per lane (a serial chain of dependent gathers per
+// thread took 125 us at 15625 particles of 3D and 31 at 10000 of 2D; now
+// 13 and 7).
+template <int D>
+__global__ __launch_bounds__(256) void k_adjm_xgather(const MoveAdjArgs a) {
+  const int j = blockIdx.x * 16 + (threadIdx.x >> 4), l = threadIdx.x & 15;
   if (j >= a.N) return;
   const bool inner = a.wall_id[j] == 0;
   const int m = min(a.ncnt[j], a.cap);
   const int64_t row = static_cast<int64_t>(j) * a.cap;
+  double s[D];
+#pragma unroll
+  for (int c = 0; c < D; ++c) s[c] = 0.0;
+  for (int e = l; e < m; e += 16) {
+    const int te = a.tidx[row + e];
+    if (te < 0) continue;
+    const double* q = a.xc + (static_cast<int64_t>(a.nidx[row + e]) * a.cap + te) * D;
+#pragma unroll
+    for (int c = 0; c < D; ++c) s[c] = s[c] + q[c];
+  }
+  const int p1 = a.wtstart[j + 1];
+  for (int p = a.wtstart[j] + l; p < p1; p += 16) {
+    const int kk = a.wt[p] >> 8, e = a.wt[p] & 0xFF;
+    const double* q = a.wxc + (static_cast<size_t>(kk) * a.cap + e) * D;
+#pragma unroll
+    for (int c = 0; c < D; ++c) s[c] = s[c] + q[c];
+  }
+  const double* own = inner ? a.xs + static_cast<size_t>(j) * D
+                            : a.wxs + static_cast<size_t>(a.wpos[j]) * D;
+#pragma unroll
   for (int c = 0; c < D; ++c) {
-    double s = a.xpass[static_cast<size_t>(c) * a.N + j];
-    if (inner) s = s + a.xs[static_cast<size_t>(j) * D + c];
-    for (int e = 0; e < m; ++e) {
-      const int te = a.tidx[row + e];
-      if (te < 0) continue;
-      const int i = a.nidx[row + e];
-      s = s + a.xc[(static_cast<int64_t>(i) * a.cap + te) * D + c];
-    }
-    for (int p = a.wtstart[j]; p < a.wtstart[j + 1]; ++p) {
-      const int kk = a.wt[p] >> 8, e = a.wt[p] & 0xFF;
-      s = s + a.wxc[(static_cast<size_t>(kk) * a.cap + e) * D + c];
-    }
-    if (!inner) s = s + a.wxs[static_cast<size_t>(a.wpos[j]) * D + c];
-    a.lam_x[static_cast<size_t>(c) * a.N + j] = s;
+    s[c] = row16_sum(s[c]);
+    const size_t o = static_cast<size_t>(c) * a.N + j;
+    if (l == 0) a.lam_x[o] = a.xpass[o] + own[c] + s[c];
   }
 }
 
@@ -830,27 +890,29 @@ hipError_t launch_adjoint_move_prep(const Ctx& c, const double* x, const double*
   return hipGetLastError();
 }
 
+template <int NC, typename Real>
+static void wallrow_t(const Ctx& c, const MoveAdjArgs& a) {
+  const Real* larr = static_cast<const Real*>(c.adj.larr);
+  const Real* f1 = static_cast<const Real*>(c.adj.f1);
+  if constexpr (sizeof(Real) == 4) {
+    if (c.cfg.nv % 4 == 0) {
+      hipLaunchKernelGGL((k_adjm_wallrow<NC, Real, 4>), dim3(c.Nw), dim3(kThreads), 0, c.stream, a,
+                         larr, f1);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_adjm_wallrow<NC, Real, 2>), dim3(c.Nw), dim3(kThreads), 0, c.stream, a,
+                     larr, f1);
+}
+
 hipError_t launch_adjoint_wallrow(const Ctx& c) {
   if (c.Nw == 0) return hipSuccess;
   const MoveAdjArgs a = move_args(c, nullptr, nullptr, nullptr, nullptr);
-  if (c.cfg.precision == BGK_FP64) {
-    const double* larr = static_cast<const double*>(c.adj.larr);
-    const double* f1 = static_cast<const double*>(c.adj.f1);
-    if (c.D == 2)
-      hipLaunchKernelGGL((k_adjm_wallrow<2, double>), dim3(c.Nw), dim3(kThreads), 0, c.stream, a,
-                         larr, f1);
-    else
-      hipLaunchKernelGGL((k_adjm_wallrow<1, double>), dim3(c.Nw), dim3(kThreads), 0, c.stream, a,
-                         larr, f1);
+  const bool f64 = c.cfg.precision == BGK_FP64;
+  if (c.D == 2) {
+    if (f64) wallrow_t<2, double>(c, a); else wallrow_t<2, float>(c, a);
   } else {
-    const float* larr = static_cast<const float*>(c.adj.larr);
-    const float* f1 = static_cast<const float*>(c.adj.f1);
-    if (c.D == 2)
-      hipLaunchKernelGGL((k_adjm_wallrow<2, float>), dim3(c.Nw), dim3(kThreads), 0, c.stream, a,
-                         larr, f1);
-    else
-      hipLaunchKernelGGL((k_adjm_wallrow<1, float>), dim3(c.Nw), dim3(kThreads), 0, c.stream, a,
-                         larr, f1);
+    if (f64) wallrow_t<1, double>(c, a); else wallrow_t<1, float>(c, a);
   }
   return hipGetLastError();
 }
@@ -912,20 +974,22 @@ hipError_t launch_adjoint_move_geometry(const Ctx& c, const void* f_n, const dou
     } else {
       if (f64) launch_ops_t<3, 1, double>(c, a, f_n, U_n); else launch_ops_t<3, 1, float>(c, a, f_n, U_n);
     }
-    const dim3 g((c.Ni + 63) / 64), b(64);
+    const dim3 g((c.Ni + 3) / 4), b(64);
     if (c.D == 2)
       hipLaunchKernelGGL(k_adjm_geom<2>, g, b, 0, c.stream, a);
     else
       hipLaunchKernelGGL(k_adjm_geom<3>, g, b, 0, c.stream, a);
   }
   if (c.Nw) {
-    const dim3 g((c.Nw + 63) / 64), b(64);
+    const dim3 g((c.Nw + 3) / 4), b(64);
     if (c.D == 2)
       hipLaunchKernelGGL(k_adjm_wallgeom<2>, g, b, 0, c.stream, a);
     else
       hipLaunchKernelGGL(k_adjm_wallgeom<3>, g, b, 0, c.stream, a);
   }
-  hipLaunchKernelGGL(k_adjm_xgather, dim3((c.N + 255) / 256), dim3(256), 0, c.stream, a, c.D);
+  const dim3 gx((c.N + 15) / 16);
+  if (c.D == 2) hipLaunchKernelGGL(k_adjm_xgather<2>, gx, dim3(256), 0, c.stream, a);
+  else hipLaunchKernelGGL(k_adjm_xgather<3>, gx, dim3(256), 0, c.stream, a);
   return hipGetLastError();
 }
 

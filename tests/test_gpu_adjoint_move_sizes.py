@@ -63,3 +63,19 @@ def test_operator_adjoint_over_grid_shapes(dim, n, nv, h, deg, precision):
         want, scale = sum(a.sum() for a in terms), sum(np.abs(a).sum() for a in terms)
         print(f"  {name}: {got:.12e} against {want:.12e}, scale {scale:.3e}", flush=True)
         assert abs(got - want) <= TOL[precision] * scale, name
+
+
+# the kernels around it that take 16 lanes or a wave per particle: clouds that
+# leave the last block of each nearly empty, rows of more than one round of
+# 16 neighbours, wall rows of more than one batch of eight, and particles in
+# the rows of many wall particles
+@pytest.mark.parametrize("dim,n,nv,h,deg,precision", [
+    (2, 5, 4, 2.2, 1, "fp64"),     # 9 interior, 16 wall particles
+    (2, 7, 4, 3.6, 2, "fp64"),
+    (2, 6, 4, 2.2, 1, "fp32"),     # 16-byte pieces of floats
+    (3, 4, 4, 2.2, 0, "fp64"),     # 8 interior, 56 wall particles
+    (3, 7, 4, 3.1, 2, "fp64"),     # over 100 neighbours
+    (3, 5, 6, 2.2, 1, "fp32"),     # 8-byte pieces of floats
+])
+def test_position_adjoint_over_cloud_shapes(dim, n, nv, h, deg, precision):
+    test_operator_adjoint_over_grid_shapes(dim, n, nv, h, deg, precision)

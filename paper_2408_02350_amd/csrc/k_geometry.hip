@@ -483,21 +483,26 @@ __device__ __forceinline__ double row_sum16(double v) {
   return v;
 }
 
-// Basis values of one scaled offset y for the fitted degree, zero beyond
-// the degree's B functions: degree 2 and 1 as Basis::eval, degree 0 the
-// offsets alone (first derivatives only, no constant).
-template <int D>
+// Basis functions of a fit of configured degree DEG.
+template <int D, int DEG>
+constexpr int wls_b() { return DEG == 0 ? D : Basis<D, DEG == 0 ? 1 : DEG>::B; }
+
+// Basis values of one scaled offset y for the fitted degree (the configured
+// one, or 1 under 2), zero beyond the degree's functions: degree 2 and 1 as
+// Basis::eval, degree 0 the offsets alone (first derivatives only, no constant).
+template <int D, int DEG>
 __device__ __forceinline__ void wls_basis(int deg, const double* y, double* p) {
-  constexpr int B2 = Basis<D, 2>::B;
-  if (deg == 2) {
+  if constexpr (DEG == 0) {
+#pragma unroll
+    for (int r = 0; r < D; ++r) p[r] = y[r];
+  } else if constexpr (DEG == 1) {
+    Basis<D, 1>::eval(y, p);
+  } else if (deg == 2) {
     Basis<D, 2>::eval(y, p);
-  } else if (deg == 1) {
+  } else {
     Basis<D, 1>::eval(y, p);
 #pragma unroll
-    for (int r = D + 1; r < B2; ++r) p[r] = 0.0;
-  } else {
-#pragma unroll
-    for (int r = 0; r < B2; ++r) p[r] = r < D ? y[r] : 0.0;
+    for (int r = D + 1; r < Basis<D, 2>::B; ++r) p[r] = 0.0;
   }
 }
 
@@ -518,26 +523,27 @@ __device__ __forceinline__ void wls_basis(int deg, const double* y, double* p) {
 // holds d+2 points, else BGK_ESINGULAR (also on a non-positive pivot).
 // Degree 0 is the fit as printed in Sec. 3.4.1: first derivatives only, the
 // basis is the scaled offsets y (no constant; the particle itself has
-// y = 0 and drops out), derivative k in column k.  A lower degree runs on
-// the degree-2 sizes with the unused basis values zero and a unit diagonal
-// in their rows of A, which leaves the fitted block and its solution as
-// they are and zeros the rest.
+// y = 0 and drops out), derivative k in column k.  The sizes are those of the
+// configured degree (bound by FP64 issue, most of it the sums and the solve:
+// degree 0 on the degree-2 sizes took 166 us at 248004 particles of 2D with 30
+// neighbours, 90 on its own; 139 and 106 at 21952 of 3D with 124).  Where
+// degree 2 falls to 1, the unused basis values are zero and their rows of A
+// have a unit diagonal, which leaves the fitted block and its solution as they
+// are and zeros the rest.
 constexpr int kWlsGroup = 4;
 constexpr int kWlsRow = kWave / kWlsGroup;
 
 // One wave's rows; nbr(i, e): entry e of particle i's neighbour row (i's m
 // entries); wls_sm: wls_smem bytes of LDS.
-template <int D, typename Count, typename Nbr>
+template <int D, int DEG, typename Count, typename Nbr>
 __device__ __forceinline__ void wls_rows(const WlsArgs& a, int pidx, bool valid, Count&& count,
                                          Nbr&& nbr, double* wls_sm) {
-  constexpr int B2 = Basis<D, 2>::B, NT2 = Basis<D, 2>::NT, DD = D * D;
+  constexpr int B = wls_b<D, DEG>(), NT = B * (B + 1) / 2, DD = D * D;
   constexpr int L = kWlsRow;
   const int lane = threadIdx.x & 63, gl = lane % L;
   const int i = valid ? a.plist[pidx] : 0;
   const int m = valid ? min(count(i), a.cap) : 0;
-  int deg = a.deg_cfg;
-  if (deg == 2 && m < 2 * B2) deg = 1;
-  const int Bg = (deg == 2) ? B2 : (deg == 1 ? D + 1 : D);
+  const int deg = DEG == 2 && m < 2 * B ? 1 : DEG;
   const bool enough = m >= D + 2;
   // per lane and local neighbour q: dl[D], W (doubles), j (int), stored
   // [q][field][lane] so that a wave's accesses are consecutive
@@ -549,9 +555,9 @@ __device__ __forceinline__ void wls_rows(const WlsArgs& a, int pidx, bool valid,
   double xi[D];
 #pragma unroll
   for (int k = 0; k < D; ++k) xi[k] = a.x[static_cast<int64_t>(k) * a.N + i];
-  double A[NT2];
+  double A[NT];
 #pragma unroll
-  for (int t = 0; t < NT2; ++t) A[t] = 0.0;
+  for (int t = 0; t < NT; ++t) A[t] = 0.0;
   for (int q = 0, e = gl; e < m; ++q, e += L) {
     const int j = nbr(i, e);
     double y[D], r2 = 0.0;
@@ -565,25 +571,26 @@ __device__ __forceinline__ void wls_rows(const WlsArgs& a, int pidx, bool valid,
     const double w = exp(-a.alpha * r2);
     WS[q * kWave + lane] = w;
     JS[q * kWave + lane] = j;
-    double p[B2];
-    wls_basis<D>(deg, y, p);
+    double p[B];
+    wls_basis<D, DEG>(deg, y, p);
 #pragma unroll
-    for (int r = 0; r < B2; ++r) {
+    for (int r = 0; r < B; ++r) {
       const double wp = w * p[r];
 #pragma unroll
       for (int s = 0; s <= r; ++s) A[tri(r, s)] = A[tri(r, s)] + wp * p[s];
     }
   }
 #pragma unroll
-  for (int t = 0; t < NT2; ++t) A[t] = row_sum16(A[t]);
+  for (int t = 0; t < NT; ++t) A[t] = row_sum16(A[t]);
+  if (deg < DEG) {
 #pragma unroll
-  for (int r = 0; r < B2; ++r)
-    if (r >= Bg) A[tri(r, r)] = 1.0;
+    for (int r = D + 1; r < B; ++r) A[tri(r, r)] = 1.0;
+  }
   // A = L L^T in place, with the reciprocals of the diagonal kept
   bool bad = false;
-  double inv[B2];
+  double inv[B];
 #pragma unroll
-  for (int jc = 0; jc < B2; ++jc) {
+  for (int jc = 0; jc < B; ++jc) {
     double s = A[tri(jc, jc)];
 #pragma unroll
     for (int k = 0; k < jc; ++k) s = s - A[tri(jc, k)] * A[tri(jc, k)];
@@ -592,7 +599,7 @@ __device__ __forceinline__ void wls_rows(const WlsArgs& a, int pidx, bool valid,
     A[tri(jc, jc)] = l;
     inv[jc] = 1.0 / l;
 #pragma unroll
-    for (int r = jc + 1; r < B2; ++r) {
+    for (int r = jc + 1; r < B; ++r) {
       double t = A[tri(r, jc)];
 #pragma unroll
       for (int k = 0; k < jc; ++k) t = t - A[tri(r, k)] * A[tri(jc, k)];
@@ -602,23 +609,23 @@ __device__ __forceinline__ void wls_rows(const WlsArgs& a, int pidx, bool valid,
   const bool ok = valid && enough && !bad;
   // z_k = A^{-1} e_col(k): derivative k is column 1 + k (degree 1 and 2) or
   // k (degree 0)
-  double z[D][B2];
+  double z[D][B];
 #pragma unroll
   for (int k = 0; k < D; ++k) {
-    const int col = deg == 0 ? k : 1 + k;
-    double yv[B2];
+    const int col = DEG == 0 ? k : 1 + k;
+    double yv[B];
 #pragma unroll
-    for (int r = 0; r < B2; ++r) {
+    for (int r = 0; r < B; ++r) {
       double s = (r == col) ? 1.0 : 0.0;
 #pragma unroll
       for (int c = 0; c < r; ++c) s = s - A[tri(r, c)] * yv[c];
       yv[r] = s * inv[r];
     }
 #pragma unroll
-    for (int r = B2 - 1; r >= 0; --r) {
+    for (int r = B - 1; r >= 0; --r) {
       double s = yv[r];
 #pragma unroll
-      for (int c = r + 1; c < B2; ++c) s = s - A[tri(c, r)] * z[k][c];
+      for (int c = r + 1; c < B; ++c) s = s - A[tri(c, r)] * z[k][c];
       z[k][r] = s * inv[r];
     }
   }
@@ -632,14 +639,14 @@ __device__ __forceinline__ void wls_rows(const WlsArgs& a, int pidx, bool valid,
         dl[k] = DL[(q * D + k) * kWave + lane];
         y[k] = dl[k] / a.h;
       }
-      double p[B2];
-      wls_basis<D>(deg, y, p);
+      double p[B];
+      wls_basis<D, DEG>(deg, y, p);
       double gk[D];
 #pragma unroll
       for (int k = 0; k < D; ++k) {
         double s = 0.0;
 #pragma unroll
-        for (int r = 0; r < B2; ++r) s = s + z[k][r] * p[r];
+        for (int r = 0; r < B; ++r) s = s + z[k][r] * p[r];
         gk[k] = w * s / a.h;
       }
       if (a.grad) {
@@ -683,13 +690,25 @@ __device__ __forceinline__ void wls_rows(const WlsArgs& a, int pidx, bool valid,
   }
 }
 
-template <int D>
+template <int D, int DEG>
 __global__ __launch_bounds__(64) void k_wls(const WlsArgs a) {
   extern __shared__ double wls_dyn[];
   const int pidx = blockIdx.x * kWlsGroup + threadIdx.x / kWlsRow;
-  wls_rows<D>(
+  wls_rows<D, DEG>(
       a, pidx, pidx < a.Ni, [&](int i) { return a.cnt[i]; },
       [&](int i, int e) { return a.idx[static_cast<int64_t>(i) * a.cap + e]; }, wls_dyn);
+}
+
+// f(D, DEG) as compile-time constants
+template <typename F>
+static void with_fit(const Ctx& c, F&& f) {
+  auto go = [&](auto d) {
+    if (c.cfg.wls_degree == 0) f(d, std::integral_constant<int, 0>{});
+    else if (c.cfg.wls_degree == 1) f(d, std::integral_constant<int, 1>{});
+    else f(d, std::integral_constant<int, 2>{});
+  };
+  if (c.D == 2) go(std::integral_constant<int, 2>{});
+  else go(std::integral_constant<int, 3>{});
 }
 
 static size_t wls_smem(int D, int cap) {
@@ -704,10 +723,9 @@ hipError_t launch_wls(const Ctx& c, const double* x, const int32_t* cnt, const i
   if (c.Ni == 0) return hipSuccess;
   const size_t sm = wls_smem(c.D, c.cap);
   const dim3 grid((c.Ni + kWlsGroup - 1) / kWlsGroup);
-  if (c.D == 2)
-    hipLaunchKernelGGL(k_wls<2>, grid, dim3(kWave), sm, c.stream, a);
-  else
-    hipLaunchKernelGGL(k_wls<3>, grid, dim3(kWave), sm, c.stream, a);
+  with_fit(c, [&](auto d, auto deg) {
+    hipLaunchKernelGGL((k_wls<d(), deg()>), grid, dim3(kWave), sm, c.stream, a);
+  });
   return hipGetLastError();
 }
 
@@ -965,7 +983,7 @@ struct GeomArgs {
   size_t off_rows, off_wls, off_psm;  // LDS offsets of a patch block
 };
 
-template <int D, int P>
+template <int D, int P, int DEG>
 __global__ __launch_bounds__(256) void k_geom_small(const GeomArgs a) {
   extern __shared__ __align__(16) unsigned char gsm[];
   const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63, cap = a.n.cap;
@@ -989,7 +1007,7 @@ __global__ __launch_bounds__(256) void k_geom_small(const GeomArgs a) {
     if (wid == 0) {
       const int g = lane / kWlsRow, pidx = b * P + g;
       const int gr = g < P ? g : 0;
-      wls_rows<D>(
+      wls_rows<D, DEG>(
           a.w, pidx, g < P && pidx < a.w.Ni, [&](int) { return rows_m[gr]; },
           [&](int, int e) { return rows[cap * gr + e]; },
           reinterpret_cast<double*>(gsm + a.off_wls));
@@ -1013,7 +1031,7 @@ __global__ __launch_bounds__(256) void k_geom_small(const GeomArgs a) {
   }
 }
 
-template <int D, int P>
+template <int D, int P, int DEG>
 static hipError_t launch_geom_t(const Ctx& c, GeomArgs a) {
   auto up = [](size_t v) { return (v + 15) / 16 * 16; };
   a.off_rows = up(static_cast<size_t>(P) * 256 * sizeof(int32_t));
@@ -1022,14 +1040,14 @@ static hipError_t launch_geom_t(const Ctx& c, GeomArgs a) {
   const size_t patch = a.off_psm + static_cast<size_t>(4) * P * c.cap * sizeof(int32_t);
   const size_t lds = std::max(patch, 4 * sizeof(ValueRowSm<D>));
   if (lds > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_geom_small<D, P>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_geom_small<D, P, DEG>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize,
                                              static_cast<int>(lds));
     if (e != hipSuccess) return e;
   }
   const unsigned nb = c.npatch + blocks_for(2 * static_cast<int64_t>(c.Nw), 4);
   if (nb == 0) return hipSuccess;
-  hipLaunchKernelGGL((k_geom_small<D, P>), dim3(nb), dim3(256), lds, c.stream, a);
+  hipLaunchKernelGGL((k_geom_small<D, P, DEG>), dim3(nb), dim3(256), lds, c.stream, a);
   return hipGetLastError();
 }
 
@@ -1047,10 +1065,15 @@ hipError_t launch_geometry_small(const Ctx& c, const double* x) {
              WallArgs{cloud_view(c, x), d.wall_list, d.wcnt, d.widx, d.wc0, d.whb, d.err},
              c.Nw, c.npatch, c.ucap, d.ucount, d.uj, d.ue, 0, 0, 0};
   hipError_t e = hipSuccess;
-  if (c.D == 2)
-    e = c.tp == 2 ? launch_geom_t<2, 2>(c, a) : launch_geom_t<2, 4>(c, a);
-  else
-    e = launch_geom_t<3, 4>(c, a);
+  with_fit(c, [&](auto d, auto deg) {
+    constexpr int D = d();
+    if constexpr (D == 2)
+      if (c.tp == 2) {
+        e = launch_geom_t<D, 2, deg()>(c, a);
+        return;
+      }
+    e = launch_geom_t<D, 4, deg()>(c, a);
+  });
   return e == hipSuccess ? launch_wall_unions(c) : e;
 }
 

@@ -55,3 +55,13 @@ def test_overflow_inside_a_small_step(dim, cap, code):
         bgk.bgk_check(ctx)
     assert e.value.code == code
     bgk.bgk_check(ctx)
+
+
+# every degree of the fit on its own sizes, in the one launch and in the
+# separate kernels (a degree-2 fit with too few neighbours falls to 1)
+@pytest.mark.parametrize("dim,n,nv,h,deg,precision", [
+    (2, 20, 4, 2.2, 0, "fp64"), (2, 86, 4, 2.2, 0, "fp64"), (2, 86, 4, 2.5, 1, "fp32"),
+    (2, 86, 4, 1.6, 2, "fp64"), (3, 8, 4, 2.2, 0, "fp64"), (3, 18, 4, 2.2, 0, "fp32"),
+    (3, 18, 4, 2.2, 1, "fp64"), (3, 18, 4, 1.5, 2, "fp64")])
+def test_moving_step_at_each_degree(dim, n, nv, h, deg, precision):
+    test_moving_step_around_the_size_limits(dim, n, nv, h, deg, precision)

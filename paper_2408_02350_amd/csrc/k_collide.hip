@@ -45,7 +45,7 @@ static inline size_t row_tab_bytes(int nv) {
 
 // A particle's row in the hands of a block: a thread takes groups of R
 // consecutive velocities along the fastest axis (16-byte row pieces; group
-// g = tid + m kThreads) and keeps its first KEEP groups (32 values) in
+// g = tid + m kThreads) and keeps its first KEEP groups (up to 32 values) in
 // registers, the whole row up to 8192 values, so that several passes read it
 // once; later groups are read again in each pass.
 template <int D, int NC, typename Real, int R, int KEEP>
@@ -135,15 +135,24 @@ __device__ __forceinline__ void row_moments(const RowGroups<D, NC, Real, R, KEEP
   T = e[0] / (3.0 * s0);
 }
 
-// with_row_groups<Real, NC>(nv, f): f(R, KEEP) as compile-time constants, for
-// 16-byte row pieces (floats: 8 bytes where 4 does not divide nv).
+// with_row_groups<Real, NC>(nv, NV, f): f(R, KEEP) as compile-time constants,
+// for 16-byte row pieces (floats: 8 bytes where 4 does not divide nv) and the
+// fewest kept values, 8, 16 or 32 per thread, that hold the row: registers
+// beyond the row's need cost resident blocks, and with them latency where a
+// cloud has few particles (relaxation of 1331 x 14^3 floats: 32 values 26.5
+// us, 16 19.2; moments of 10000 x 24^2 x 2 doubles: 32 values 39, 8 35).
 template <typename Real, int NC, typename F>
-static void with_row_groups(int nv, F&& f) {
+static void with_row_groups(int nv, int NV, F&& f) {
+  auto keep = [&](auto r) {
+    constexpr int R = r();
+    const int64_t row = static_cast<int64_t>(NC) * NV;
+    if (row <= 8 * kThreads) f(r, std::integral_constant<int, 8 / (R * NC)>{});
+    else if (row <= 16 * kThreads) f(r, std::integral_constant<int, 16 / (R * NC)>{});
+    else f(r, std::integral_constant<int, 32 / (R * NC)>{});
+  };
   if constexpr (sizeof(Real) == 4)
-    if (nv % 4 == 0)
-      return f(std::integral_constant<int, 4>{}, std::integral_constant<int, 32 / (4 * NC)>{});
-  f(std::integral_constant<int, 2>{},
-    std::integral_constant<int, 32 / (2 * NC)>{});
+    if (nv % 4 == 0) return keep(std::integral_constant<int, 4>{});
+  keep(std::integral_constant<int, 2>{});
 }
 
 struct CollideArgs {
@@ -209,7 +218,7 @@ __global__ __launch_bounds__(kThreads) void k_collide(const CollideArgs a) {
 template <typename Real, int D, int NC>
 static void collide_t(const Ctx& c, const CollideArgs& a) {
   const size_t lds = row_tab_bytes<D>(c.cfg.nv);
-  with_row_groups<Real, NC>(c.cfg.nv, [&](auto r, auto keep) {
+  with_row_groups<Real, NC>(c.cfg.nv, c.NV, [&](auto r, auto keep) {
     hipLaunchKernelGGL((k_collide<D, NC, Real, r(), keep()>), dim3(a.count), dim3(kThreads), lds,
                        c.stream, a);
   });
@@ -716,7 +725,7 @@ __global__ __launch_bounds__(kThreads) void k_moments(int N, int NV, int nv, dou
 template <int D, int NC, typename Real>
 static void moments_t(const Ctx& c, const void* f, double* rho, double* U, double* T) {
   const size_t lds = static_cast<size_t>(c.cfg.nv) * sizeof(double);
-  with_row_groups<Real, NC>(c.cfg.nv, [&](auto r, auto keep) {
+  with_row_groups<Real, NC>(c.cfg.nv, c.NV, [&](auto r, auto keep) {
     hipLaunchKernelGGL((k_moments<D, NC, Real, r(), keep()>), dim3(c.N), dim3(kThreads), lds,
                        c.stream, c.N, c.NV, c.cfg.nv, c.cfg.vmax, omega_of(c.cfg), f, rho, U, T);
   });
@@ -866,7 +875,7 @@ template <int D, int NC, typename Real>
 static void state_check_t(const Ctx& c, const void* f, const double* rho, const double* U,
                           const double* T, double* out_dev) {
   const size_t lds = static_cast<size_t>(c.cfg.nv) * sizeof(double);
-  with_row_groups<Real, NC>(c.cfg.nv, [&](auto r, auto keep) {
+  with_row_groups<Real, NC>(c.cfg.nv, c.NV, [&](auto r, auto keep) {
     hipLaunchKernelGGL((k_state_terms<D, NC, Real, r(), keep()>), dim3(c.N), dim3(kThreads), lds,
                        c.stream, c.N, c.NV, c.cfg.nv, c.cfg.vmax, omega_of(c.cfg), f, rho, U, T,
                        c.d.scheck);

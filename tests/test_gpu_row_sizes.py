@@ -1,5 +1,5 @@
-"""Row kernels (moments, their adjoint, the objective's gradient, the state
-check) over the row shapes their groups of velocities distinguish: the
+"""Row kernels (moments, relaxation, the moments' adjoint, the objective's
+gradient, the state check) over the row shapes their groups of velocities distinguish: the
 smallest grid, 8- and 16-byte pieces, rows longer than a block keeps in
 registers, and rows that start at an address of 8 (4) bytes only."""
 import numpy as np
@@ -28,9 +28,14 @@ def shifted(a):
 @pytest.mark.parametrize("dim,n,nv,precision", [
     (2, 5, 2, "fp64"),
     (2, 5, 24, "fp64"),
+    (2, 5, 40, "fp64"),    # 3200 values a row
     (2, 5, 66, "fp64"),    # 8712 values a row
     (2, 5, 18, "fp32"),    # 8-byte pieces
     (2, 5, 96, "fp32"),    # 18432 values a row
+    (3, 4, 14, "fp32"),    # 2744 values a row
+    (3, 4, 16, "fp32"),    # 4096 values a row, 16-byte pieces
+    (3, 4, 16, "fp64"),
+    (3, 4, 18, "fp64"),    # 5832 values a row
     (3, 4, 22, "fp64"),    # 10648 values a row
     (3, 4, 22, "fp32"),
     (3, 4, 24, "fp32"),    # 13824 values a row, 16-byte pieces
@@ -59,6 +64,18 @@ def test_row_kernels_over_row_shapes(dim, n, nv, precision):
     print("  check", chk, flush=True)
     assert chk["min_f"] == f.min() and chk["negatives"] == 0 and chk["nonfinite"] == 0
     assert max(chk["rho_residual"], chk["U_residual"], chk["T_residual"]) <= 1e-13
+    # the relaxation: one rounding of a value of at most the field's maximum
+    bgk.bgk_geometry(ctx, t(x))
+    out = shifted(torch.zeros_like(ft))
+    rel = [a.clone() for a in got]
+    bgk.bgk_collide(ctx, ft, out, *rel)
+    fo, ro, Uo, To = oracle.collide(c, wid, f)
+    inner = wid == 0
+    eps = 1e-13 if precision == "fp64" else 1e-7
+    assert np.abs(out.double().cpu().numpy() - fo)[:, inner].max() <= eps * np.abs(fo).max()
+    for a, b in zip((ro, Uo, To), rel):
+        np.testing.assert_allclose(b.cpu().numpy()[..., inner], a[..., inner], rtol=1e-12,
+                                   atol=1e-13)
     # the moments' derivative in float64, added to a row of lam_f: FP64 1e-12
     # of the sum of absolute terms; FP32 storage rounds the sum once (6e-8)
     fa = torch.from_numpy(f).requires_grad_(True)

@@ -282,11 +282,15 @@ __global__ __launch_bounds__(kThreads) void k_adj_wall(const AdjArgs<Real> a) {
 // Pass 1 gathers the adjoint of f' (lam_f1 plus what the wall rows that
 // interpolate from the particle send back) and reduces the D+3 sums of the
 // relaxation's and the moments' adjoint; pass 2 writes lam_ft.  The first
-// KEEP groups of a thread keep the adjoint of f' in registers between the
-// passes, in the storage precision (the whole row at the configured grids);
-// later groups are gathered again, or, near a wall, read back from the
-// particle's own lam_ft row, where pass 1 left them (same thread, same
-// velocities; nothing else reads the row).
+// KEEP groups of a thread are loaded, with f-tilde's, before the tables are
+// formed, and keep the adjoint of f' in registers between the passes, in the
+// storage precision (as few values as hold the row: up to 4096 doubles or
+// 8192 floats); later groups are gathered again, or, near a wall, read back
+// from the particle's own lam_ft row, where pass 1 left them (same thread,
+// same velocities; nothing else reads the row).  Bound by HBM (two rows read,
+// one written) and the latency of a block's phases: 9604 x 24^2 x 2 doubles
+// 84 -> 68 us, 12167 x 14^3 doubles 312 -> 278, 97336 x 20^3 floats 2.52 ->
+// 2.50 ms, against a load of each group right before its use.
 template <int D, int NC, typename Real, int R, int KEEP>
 __global__ __launch_bounds__(kThreads) void k_adj_collide(const AdjArgs<Real> a) {
   __shared__ double sh[4 * (D + 4)];
@@ -312,6 +316,21 @@ __global__ __launch_bounds__(kThreads) void k_adj_collide(const AdjArgs<Real> a)
   const int ws = a.wtstart[i], we = a.wtstart[i + 1];
   const int nv = a.nv, ng0 = nv / R, ng = a.NV / R;
   double* et = vt + nv;
+  const Real* __restrict__ l1 = a.lam_f1 + static_cast<size_t>(i) * NVs;
+  const Real* __restrict__ xr = a.ft + static_cast<size_t>(i) * NVs;
+  // both rows' kept groups in flight behind the tables
+  Real lk[KEEP][NC][R], xk[KEEP][NC][R];
+#pragma unroll
+  for (int m = 0; m < KEEP; ++m) {
+    const int g = threadIdx.x + m * kThreads;
+    if (g < ng) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        load_rs<Real, R>(l1 + c * cs + static_cast<size_t>(g) * R, lk[m][c]);
+        load_rs<Real, R>(xr + c * cs + static_cast<size_t>(g) * R, xk[m][c]);
+      }
+    }
+  }
   for (int k = threadIdx.x; k < nv; k += blockDim.x) vt[k] = vnode(k, nv, a.vmax);
   __syncthreads();
   for (int t = threadIdx.x; t < D * nv; t += blockDim.x) {
@@ -322,8 +341,6 @@ __global__ __launch_bounds__(kThreads) void k_adj_collide(const AdjArgs<Real> a)
   __syncthreads();
   const double tp = 2.0 * kPi * T;
   const double norm = D == 3 ? rho / (tp * sqrt(tp)) : rho / tp;
-  const Real* __restrict__ l1 = a.lam_f1 + static_cast<size_t>(i) * NVs;
-  const Real* __restrict__ xr = a.ft + static_cast<size_t>(i) * NVs;
   Real* __restrict__ lrow = a.lam_ft + static_cast<size_t>(i) * NVs;
   const bool near = we > ws;
   // the slower axes of a group: their offsets w_a, sum w_a^2, prod e_a
@@ -338,9 +355,9 @@ __global__ __launch_bounds__(kThreads) void k_adj_collide(const AdjArgs<Real> a)
       Ms = Ms * et[k * nv + kd[k]];
     }
   };
-  // adjoint of f' at a group's R nodes (component c), rounded to storage
+  // adjoint of f' at a group's R nodes (component c) from lam_f1's, rounded to
+  // storage: what the wall rows send back is added
   auto gather = [&](int c, size_t q, Real (&o)[R]) {
-    load_rs<Real, R>(l1 + c * cs + q, o);
     if (!near) return;
     double l[R];
 #pragma unroll
@@ -359,12 +376,9 @@ __global__ __launch_bounds__(kThreads) void k_adj_collide(const AdjArgs<Real> a)
   double s[D + 3];  // A1 = sum l M, A2 = sum l (ft - M), AU[d], AT
 #pragma unroll
   for (int k = 0; k < D + 3; ++k) s[k] = 0.0;
-  auto accum = [&](size_t q, const int (&kd)[D], const Real (&lq)[NC][R]) {
+  auto accum = [&](const int (&kd)[D], const Real (&lq)[NC][R], const Real (&xq)[NC][R]) {
     double w[3], w2s, Ms;
     slow(kd, w, w2s, Ms);
-    Real xq[NC][R];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) load_rs<Real, R>(xr + c * cs + q, xq[c]);
     const int k0 = kd[0] * R;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -386,7 +400,6 @@ __global__ __launch_bounds__(kThreads) void k_adj_collide(const AdjArgs<Real> a)
       }
     }
   };
-  Real lk[KEEP][NC][R];
   {
     GroupDigits<D> gd;
     gd.init(threadIdx.x, kThreads, ng0, nv);
@@ -397,19 +410,21 @@ __global__ __launch_bounds__(kThreads) void k_adj_collide(const AdjArgs<Real> a)
         const size_t q = static_cast<size_t>(g) * R;
 #pragma unroll
         for (int c = 0; c < NC; ++c) gather(c, q, lk[m][c]);
-        accum(q, gd.k, lk[m]);
+        accum(gd.k, lk[m], xk[m]);
       }
       gd.advance(ng0, nv);
     }
     for (; g < ng; g += kThreads) {
       const size_t q = static_cast<size_t>(g) * R;
-      Real lq[NC][R];
+      Real lq[NC][R], xq[NC][R];
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
+        load_rs<Real, R>(l1 + c * cs + q, lq[c]);
+        load_rs<Real, R>(xr + c * cs + q, xq[c]);
         gather(c, q, lq[c]);
         if (near) store_rs<Real, R>(lrow + c * cs + q, lq[c]);
       }
-      accum(q, gd.k, lq);
+      accum(gd.k, lq, xq);
       gd.advance(ng0, nv);
     }
   }
@@ -1131,16 +1146,20 @@ static hipError_t launch_adj_patch(const Ctx& c, const AdjArgs<Real>& a, const A
 // divides nv), and 32 registers of the adjoint of f' kept per thread.
 template <int D, int NC, typename Real>
 static void launch_adj_collide(const Ctx& c, const AdjArgs<Real>& a, dim3 t, size_t lds) {
-  constexpr int W = static_cast<int>(sizeof(Real)) / 4;
-  if constexpr (W == 1) {
-    if (c.cfg.nv % 4 == 0) {
-      constexpr int R = 4, KEEP = 32 / (R * NC);
-      hipLaunchKernelGGL((k_adj_collide<D, NC, Real, R, KEEP>), dim3(c.Ni), t, lds, c.stream, a);
-      return;
-    }
-  }
-  constexpr int R = 2, KEEP = 32 / (R * NC * W);
-  hipLaunchKernelGGL((k_adj_collide<D, NC, Real, R, KEEP>), dim3(c.Ni), t, lds, c.stream, a);
+  auto go = [&](auto r, auto keep) {
+    hipLaunchKernelGGL((k_adj_collide<D, NC, Real, r(), keep()>), dim3(c.Ni), t, lds, c.stream, a);
+  };
+  auto keep = [&](auto r) {
+    constexpr int R = r();
+    const int64_t row = static_cast<int64_t>(NC) * c.NV;
+    if (row <= 8 * kThreads) return go(r, std::integral_constant<int, 8 / (R * NC)>{});
+    if constexpr (std::is_same<Real, float>::value)
+      if (row > 16 * kThreads) return go(r, std::integral_constant<int, 32 / (R * NC)>{});
+    go(r, std::integral_constant<int, 16 / (R * NC)>{});
+  };
+  if constexpr (std::is_same<Real, float>::value)
+    if (c.cfg.nv % 4 == 0) return keep(std::integral_constant<int, 4>{});
+  keep(std::integral_constant<int, 2>{});
 }
 
 template <typename Real>

@@ -44,9 +44,11 @@ def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
 
-# Sources the fused kernel's machine code depends on: a traffic figure measured
+# Sources the transport kernels' machine code depends on: a traffic figure measured
 # with counters is reported only while these are unchanged.
 TRAFFIC_SOURCES = ("paper_2408_02350_amd/csrc/k_fused.hip",
+                   "paper_2408_02350_amd/csrc/k_walk.hip",
+                   "paper_2408_02350_amd/csrc/k_collide.hip",
                    "paper_2408_02350_amd/csrc/device_common.h",
                    "paper_2408_02350_amd/csrc/bgk_internal.h")
 
@@ -61,7 +63,7 @@ def kernel_source_hash():
 
 
 def measured_traffic(workload, precision):
-    """HBM bytes per launch of the fused kernel from the committed counter
+    """HBM bytes per launch of the transport and relaxation from the committed counter
     summary (FETCH_SIZE and WRITE_SIZE scaled by a plain copy), or None when
     there is none for this workload or the kernel source changed since."""
     import glob
@@ -482,7 +484,10 @@ def main():
     else:
         roof = {"bound": "hbm", "achieved": ach_gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": ach_gbs / PEAK_HBM_GBS}
-    roof.update({"traffic": measured_traffic(cav.name, args.precision), "kernel": "k_fused",
+    # (3D FP64 grids of several tiles take the transport and the relaxation apart)
+    walk = cav.dim == 3 and args.precision == "fp64" and cav.n_velocities > 6144
+    roof.update({"traffic": measured_traffic(cav.name, args.precision),
+                 "kernel": "k_walk + k_collide" if walk else "k_fused",
                  "kernel_ms": k_ms, "kernel_updates_per_s": updates / (k_ms * 1e-3),
                  "algorithmic_bytes": bytes_, "algorithmic_ops": ops, "ops_per_update": k,
                  "hbm_frac": ach_gbs / PEAK_HBM_GBS, "alu_frac": ach_tops / PEAK_VALU_TOPS,

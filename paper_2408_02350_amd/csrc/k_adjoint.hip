@@ -641,8 +641,9 @@ __global__ __launch_bounds__(64) void k_adj_transport_wall(const AdjArgs<Real> a
 // are loaded right before their use, since a second row buffer's registers
 // cost a wave per SIMD (2D FP64 R = 3 at 168 registers and 3 waves, FP32 at
 // 124 and 4).  9604 interior particles x 24^2, per launch: FP64 271 -> 223 us
-// (R 4 -> 3: full tiles), FP32 171 -> 144; 23^3 x 14^3 FP64 2.85 -> 2.30 ms
-// (R 2 -> 5, ragged), 30^3 x 20^3 13.4 -> 12.0 (R 4 -> 5).
+// (R 4 -> 3: full tiles), FP32 171 -> 144; 3D one particle per patch:
+// 23^3 x 14^3 FP64 2.85 -> 2.10 ms (R 2 -> 7), x 20^3 6.3 -> 5.4 (R 4 -> 5),
+// 46^3 x 20^3 FP32 22.7 -> 22.3.
 constexpr int kAdjUChunk = 32;
 
 
@@ -1133,7 +1134,7 @@ hipError_t launch_adjoint_transposes(const Ctx& c) {
 template <int D, int NC, typename Real, int R>
 static hipError_t launch_adj_patch(const Ctx& c, const AdjArgs<Real>& a, const AdjPlan& ap,
                                    int npa) {
-  constexpr int P = 2;
+  constexpr int P = D == 3 ? 1 : 2;
   if (ap.P != P) return hipErrorInvalidValue;
   const int64_t nb = static_cast<int64_t>(npa) * ap.tiles;
   if (nb > INT32_MAX) return hipErrorInvalidValue;
@@ -1227,7 +1228,10 @@ static hipError_t adjoint_step_t(const Ctx& c, const Real* f_n, const double* U_
     if (npa) {
       if (R == 5) e = launch_adj_patch<3, 1, Real, 5>(c, a, ap, npa);
       if constexpr (std::is_same<Real, double>::value)
-        if (R == 3) e = launch_adj_patch<3, 1, Real, 3>(c, a, ap, npa);
+        e = R == 6   ? launch_adj_patch<3, 1, Real, 6>(c, a, ap, npa)
+            : R == 7 ? launch_adj_patch<3, 1, Real, 7>(c, a, ap, npa)
+            : R == 3 ? hipErrorInvalidValue  // (the plan takes 3 in 2D only)
+                     : e;
       if (R == 4) e = launch_adj_patch<3, 1, Real, 4>(c, a, ap, npa);
       if (R == 2) e = launch_adj_patch<3, 1, Real, 2>(c, a, ap, npa);
     }

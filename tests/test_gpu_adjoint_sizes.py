@@ -30,10 +30,12 @@ def t(a, dtype=torch.float64):
     (2, 7, 22, "fp64"),    # 3 per lane, overlaps by 2, a nearly empty tile
     (2, 6, 24, "fp64"),    # 3 per lane, full tiles
     (2, 6, 36, "fp32"),
+    (3, 5, 6, "fp64"),     # 2 per lane
     (3, 5, 8, "fp64"),     # 4 per lane
     (3, 5, 10, "fp64"),    # 5 per lane
-    (3, 5, 14, "fp64"),    # 5 per lane, overlaps by 1
-    (3, 5, 18, "fp64"),    # 5 per lane, overlaps by 2
+    (3, 5, 14, "fp64"),    # 7 per lane
+    (3, 5, 18, "fp64"),    # 6 per lane
+    (3, 4, 22, "fp64"),    # 6 per lane, overlaps by 2
     (3, 5, 10, "fp32"),
 ])
 def test_adjoint_step_over_lane_widths(dim, n, nv, precision):

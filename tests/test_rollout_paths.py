@@ -1,0 +1,121 @@
+"""What a rollout holds between its two passes, on the CPU: the library calls
+are stand-ins that read and write through the tensors' storage, as the library
+does, so that no tensor's version tells of a write."""
+import types
+
+import pytest
+import torch
+
+import paper_2408_02350_amd.adjoint as A
+
+F64 = torch.float64
+
+
+def put(dst, src):
+    dst.detach().numpy()[...] = src.detach().numpy()  # the version of dst stays
+
+
+class Kernels:
+    """A step f' = c f + a U f^2 + lid, U' = mean f, and its adjoint, exact."""
+    c, a = 0.9, 0.05
+
+    def __init__(self):
+        self.lid, self.calls = 0.0, []
+
+    def bgk_set_lid_velocity(self, ctx, lid):
+        self.lid = lid
+
+    def bgk_moments(self, ctx, f):
+        return f.new_ones(1), f.detach().mean().reshape(1, 1), f.new_ones(1)
+
+    def bgk_step(self, ctx, f, fn, x, U, rho, T):
+        self.calls.append("step")
+        out = self.c * f + self.a * U * f * f + self.lid + 0.01 * x.sum()
+        put(fn, out)
+        put(U, out.mean().reshape(1, 1))
+        if ctx.moves:
+            put(x, x * 1.01)
+
+    def bgk_step_keep(self, ctx, f, fn, x, U, rho, T, ft):
+        self.bgk_step(ctx, f, fn, x, U, rho, T)
+        put(ft, f)
+
+    def bgk_objective(self, ctx, f, rho, U, ke, want_grad):
+        J = (f * f).sum()
+        return (J, (2 * f, torch.zeros_like(rho), torch.zeros_like(U))) if want_grad else J
+
+    def bgk_adjoint_step(self, ctx, f, U, x, l1, lU1, lr, lT, lf, lU, dlid):
+        g = l1 + lU1 / f.numel()
+        put(dlid, dlid + g.sum())
+        put(lU, (g * self.a * f * f).sum().reshape(1, 1))
+        put(lf, g * (self.c + 2 * self.a * U * f))
+
+    def bgk_adjoint_step_kept(self, ctx, f, U, x, kept, *rest):
+        assert torch.equal(kept[0], f)
+        self.bgk_adjoint_step(ctx, f, U, x, *rest)
+
+    def bgk_adjoint_step_move(self, ctx, f, U, x, l1, lU1, lx1, lr, lT, lf, lU, lx, dlid):
+        g = (l1 + lU1 / f.numel()).sum()
+        put(lx, 1.01 * lx1 + 0.01 * g)
+        self.bgk_adjoint_step(ctx, f, U, x, l1, lU1, lr, lT, lf, lU, dlid)
+
+    def bgk_moments_adjoint(self, ctx, rho, U, T, lf, lr, lU, lT):
+        put(lf, lf + lU / lf.numel())
+
+
+@pytest.fixture
+def kernels(monkeypatch):
+    k = Kernels()
+    monkeypatch.setattr(A, "B", k)
+    monkeypatch.setattr(A, "_room", lambda nbytes, device: True)
+    return k
+
+
+def problem(kind):
+    base = A.MovingCavity if kind == "moving" else A.FrozenCavity
+    p = object.__new__(base)
+    p.ctx = types.SimpleNamespace(device="cpu", moves=kind == "moving")
+    p.N, p.keep_states = 1, kind != "states"
+    p.x = p.x0 = torch.full((1, 1), 0.5, dtype=F64)
+    return p
+
+
+def inputs():
+    f0 = torch.linspace(0.5, 1.5, 6, dtype=F64).requires_grad_(True)
+    return f0, torch.tensor(0.1, dtype=F64, requires_grad=True)
+
+
+def rollout(p, f0, lid, nsteps, every):
+    call = A.rollout_objective_move if isinstance(p, A.MovingCavity) else A.rollout_objective
+    return call(p, f0, lid, nsteps, every)
+
+
+KINDS = ["kept", "states", "moving"]
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("nsteps,every", [(3, 3), (5, 2)])
+def test_a_write_into_f0_before_the_backward_does_not_reach_the_steps(kernels, kind, nsteps, every):
+    # (the moments of f^0, which enter its own gradient alone, are the caller's)
+    p = problem(kind)
+    f0, lid = inputs()
+    want, = torch.autograd.grad(rollout(p, f0, lid, nsteps, every), lid)
+    J = rollout(p, f0, lid, nsteps, every)
+    put(f0, 3 * f0)
+    for _ in range(2):
+        assert torch.equal(torch.autograd.grad(J, lid, retain_graph=True)[0], want)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("nsteps,every", [(3, 3), (5, 2)])
+def test_copying_hooks_hold_f0_as_it_was(kernels, kind, nsteps, every):
+    p = problem(kind)
+    f0, lid = inputs()
+    want = torch.autograd.grad(rollout(p, f0, lid, nsteps, every), [f0, lid])
+    with torch.autograd.graph.saved_tensors_hooks(torch.clone, lambda t: t):
+        J = rollout(p, f0, lid, nsteps, every)
+    with torch.no_grad():
+        f0.mul_(3)
+    for _ in range(2):
+        got = torch.autograd.grad(J, [f0, lid], retain_graph=True)
+        assert all(torch.equal(a, b) for a, b in zip(got, want))

@@ -45,37 +45,32 @@ def _room(nbytes: int, device) -> bool:
             and 4 * nbytes <= torch.cuda.mem_get_info(device)[0])
 
 
-class _Run:
-    """The forward pass of a rollout for its backward: the last segment's
-    steps (from first_kept on) kept if there is room, the start of every
-    segment in ``saved``.  f^0 is copied: the caller's storage may have been
-    written through its pointer by the time the backward pass reads it, which
-    autograd's version counter does not see, and under saved-tensor hooks no
-    version is looked at (110592 x 20^3 floats: 1.5 of 115 ms)."""
+def _march(step, f, nsteps, every, *state):
+    """nsteps calls step(f, f_next) from f, which is taken over; they advance
+    ``state`` in place.  Returns the final f and {s: (f, *state)} of every
+    segment start s (every None: of none)."""
+    starts = {s0 for s0, _ in segments(nsteps, every)} if every else set()
+    saved, spare = {}, None
+    for s in range(nsteps):
+        fn = torch.empty_like(f) if spare is None else spare
+        spare = f
+        if s in starts:
+            saved[s] = (f, *(t.clone() for t in state))
+            spare = None
+        step(f, fn)
+        f = fn
+    return f, saved
 
-    def __init__(self, f0, nsteps, every, keep, fields, device):
-        segs = segments(nsteps, every) if every else []
-        self.starts = {s0 for s0, _ in segs}
-        self.f = f0.detach().clone()
-        self.first_kept = nsteps
-        if keep and segs:
-            s0, s1 = segs[-1]
-            if _room(fields * (s1 - s0) * self.f.numel() * self.f.element_size(), device):
-                self.first_kept = s0
-        self.saved = {}
-        self.spare = None
 
-    def save(self, s, *more):
-        self.saved[s] = (self.f, *(t.clone() for t in more))
-
-    def step(self, s, call, *state):
-        """Step s by call(f, f_next); state: what a segment start saves."""
-        if s in self.starts:
-            self.save(s, *state)
-        fn = torch.empty_like(self.f) if self.spare is None else self.spare
-        call(self.f, fn)
-        self.spare = self.f if s not in self.starts else None
-        self.f = fn
+def _tail(p, f0, nsteps, every, keep, fields):
+    """Steps at the end of a rollout that the forward pass keeps for the
+    backward, ``fields`` f-sized arrays each: the last segment, or none where
+    no gradient is wanted, there is no room, or the problem's own forward()
+    has to be asked for the whole rollout."""
+    if not (keep and every) or nsteps <= 0 or getattr(p.forward, "__func__", None) not in _FORWARD:
+        return 0
+    s0, s1 = segments(nsteps, every)[-1]
+    return s1 - s0 if _room(fields * (s1 - s0) * f0.numel() * f0.element_size(), p.ctx.device) else 0
 
 
 class FrozenCavity:
@@ -120,16 +115,14 @@ class FrozenCavity:
         (f, rho, U, T) and the (f, U) stored at each segment start."""
         c = self.ctx
         B.bgk_set_lid_velocity(c, float(lid))
+        # (a copy: by the time the backward pass reads f^0 the caller's storage
+        # may have been written through its pointer, which autograd's version
+        # counter does not see, and under saved-tensor hooks no version is
+        # looked at; 110592 x 20^3 floats: 1.5 of 115 ms)
         f = f0.detach().clone()
         rho, U, T = B.bgk_moments(c, f)
-        fn = torch.empty_like(f)
-        starts = {s0 for s0, _ in segments(nsteps, every)} if every else set()
-        saved = {}
-        for s in range(nsteps):
-            if s in starts:
-                saved[s] = (f.clone(), U.clone())
-            B.bgk_step(c, f, fn, self.x, U, rho, T)
-            f, fn = fn, f
+        f, saved = _march(lambda f, fn: B.bgk_step(c, f, fn, self.x, U, rho, T), f, nsteps, every,
+                          U)
         return (f, rho, U, T), saved
 
     def objective(self, f0, lid, nsteps, ke_weight=1.0):
@@ -169,29 +162,23 @@ class _Rollout(torch.autograd.Function):
     @staticmethod
     def forward(actx, f0, lid, problem, nsteps, every, ke_weight, keep=False):
         p, c = problem, problem.ctx
-        B.bgk_set_lid_velocity(c, float(lid))
-        r = _Run(f0, nsteps, every, keep, 2 if p.keep_states else 1, c.device)
-        rho, U, T = B.bgk_moments(c, r.f)
-        for s in range(r.first_kept):
-            r.step(s, lambda f, fn: B.bgk_step(c, f, fn, p.x, U, rho, T), U)
+        n = _tail(p, f0, nsteps, every, keep, 2 if p.keep_states else 1)
+        (f, rho, U, T), saved = p.forward(f0, lid, nsteps - n, every)
         last = None
-        if r.first_kept < nsteps:
-            r.save(r.first_kept, U)
-            n, U0 = nsteps - r.first_kept, U.clone()
+        if n:
+            saved[nsteps - n] = (f, U.clone())
             if p.keep_states:
-                last = _kept_segment(p, r.f, U0, n)
+                last = _kept_segment(p, f, saved[nsteps - n][1], n)
                 _, f, rho, U, _ = last[-1][2]
             else:
-                last = _states(lambda f, fn, st: B.bgk_step(c, f, fn, p.x, st[0], rho, T),
-                               r.f, (U0,), n)
-                f, U = torch.empty_like(r.f), last[-1][1].clone()
+                last = _states(lambda f, fn, st: B.bgk_step(c, f, fn, p.x, st[0], rho, T), f, (U,),
+                               n)
+                f, U = torch.empty_like(f), last[-1][1].clone()
                 B.bgk_step(c, last[-1][0], f, p.x, U, rho, T)
-        else:
-            f = r.f
         J = B.bgk_objective(c, f, rho, U, ke_weight, want_grad=False)
         actx.problem, actx.nsteps, actx.every, actx.ke = problem, nsteps, every, ke_weight
         actx.final = (f, rho, U)
-        actx.saved, actx.last = r.saved, last
+        actx.saved, actx.last = saved, last
         actx.lid = float(lid)
         actx.save_for_backward(f0)
         return J
@@ -289,14 +276,7 @@ class MovingCavity:
         f = f0.detach().clone()
         x = (self.x0 if x0 is None else x0).detach().clone()
         rho, U, T = B.bgk_moments(c, f)
-        fn = torch.empty_like(f)
-        starts = {s0 for s0, _ in segments(nsteps, every)} if every else set()
-        saved = {}
-        for s in range(nsteps):
-            if s in starts:
-                saved[s] = (f.clone(), U.clone(), x.clone())
-            B.bgk_step(c, f, fn, x, U, rho, T)
-            f, fn = fn, f
+        f, saved = _march(lambda f, fn: B.bgk_step(c, f, fn, x, U, rho, T), f, nsteps, every, U, x)
         return (f, rho, U, T, x), saved
 
     def objective(self, f0, lid, nsteps, ke_weight=1.0, x0=None):
@@ -306,28 +286,28 @@ class MovingCavity:
         return float(J.item())
 
 
+# the forward passes that a rollout may cut short of its last segment
+_FORWARD = (FrozenCavity.forward, MovingCavity.forward)
+
+
 class _RolloutMove(torch.autograd.Function):
     @staticmethod
     def forward(actx, f0, lid, x0, problem, nsteps, every, ke_weight, keep=False):
         p, c = problem, problem.ctx
-        B.bgk_set_lid_velocity(c, float(lid))
-        r = _Run(f0, nsteps, every, keep, 1, c.device)
-        x = x0.detach().clone()
-        rho, U, T = B.bgk_moments(c, r.f)
-        for s in range(r.first_kept):
-            r.step(s, lambda f, fn: B.bgk_step(c, f, fn, x, U, rho, T), U, x)
-        f, last = r.f, None
-        if r.first_kept < nsteps:
-            r.save(r.first_kept, U, x)
-            last = _states(lambda f, fn, st: B.bgk_step(c, f, fn, st[1], st[0], rho, T),
-                           r.f, (U, x), nsteps - r.first_kept)
+        n = _tail(p, f0, nsteps, every, keep, 1)
+        (f, rho, U, T, x), saved = p.forward(f0, lid, nsteps - n, every, x0)
+        last = None
+        if n:
+            saved[nsteps - n] = (f, U.clone(), x.clone())
+            last = _states(lambda f, fn, st: B.bgk_step(c, f, fn, st[1], st[0], rho, T), f, (U, x),
+                           n)
             fa, U, x = last[-1][0], last[-1][1].clone(), last[-1][2].clone()
             f = torch.empty_like(fa)
             B.bgk_step(c, fa, f, x, U, rho, T)
         J = B.bgk_objective(c, f, rho, U, ke_weight, want_grad=False)
         actx.problem, actx.nsteps, actx.every, actx.ke = problem, nsteps, every, ke_weight
         actx.final = (f, rho, U)
-        actx.saved, actx.last = r.saved, last
+        actx.saved, actx.last = saved, last
         actx.lid = float(lid)
         actx.save_for_backward(f0)
         return J

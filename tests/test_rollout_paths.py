@@ -119,3 +119,24 @@ def test_copying_hooks_hold_f0_as_it_was(kernels, kind, nsteps, every):
     for _ in range(2):
         got = torch.autograd.grad(J, [f0, lid], retain_graph=True)
         assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("where", ["class", "instance"])
+def test_a_problem_with_its_own_forward_is_asked_for_the_whole_rollout(kernels, kind, where):
+    p = problem(kind)
+    own, seen = type(p).forward, []
+
+    def forward(self, f0, lid, nsteps, every=None, *more):
+        seen.append((nsteps, every))
+        return own(self, f0, lid, nsteps, every, *more)
+
+    f0, lid = inputs()
+    want = torch.autograd.grad(rollout(p, f0, lid, 3, 2), [f0, lid])
+    if where == "class":
+        p.__class__ = type("Own", (type(p),), {"forward": forward})
+    else:
+        p.forward = types.MethodType(forward, p)
+    got = torch.autograd.grad(rollout(p, f0, lid, 3, 2), [f0, lid])
+    assert seen == [(3, 2)]
+    assert all(torch.equal(a, b) for a, b in zip(got, want))

@@ -17,7 +17,10 @@ array per step, twice the forward work; the same gradients bit for bit).
 The last segment, which the backward pass walks first, is run by the forward
 pass in the same way where its arrays take at most a quarter of the free
 device memory, and is not recomputed (3 steps of 48^3 x 20^3 FP32 in one
-segment 151 -> 118 ms, 20 of 100^2 x 24^2 FP64 in two 11.1 -> 10.1).
+segment 151 -> 118 ms, 20 of 100^2 x 24^2 FP64 in two 11.1 -> 10.1).  They
+stay allocated until the backward pass or the end of the graph; a program
+that needs the memory in between turns this off with ``keep_states=False``,
+under which nothing but the segment starts is held between the passes.
 All arithmetic runs in libbgk; torch only holds the buffers.
 """
 from __future__ import annotations
@@ -65,9 +68,9 @@ def _march(step, f, nsteps, every, *state):
 def _tail(p, f0, nsteps, every, keep, fields):
     """Steps at the end of a rollout that the forward pass keeps for the
     backward, ``fields`` f-sized arrays each: the last segment, or none where
-    no gradient is wanted, there is no room, or the problem's own forward()
-    has to be asked for the whole rollout."""
-    if not (keep and every) or nsteps <= 0 or getattr(p.forward, "__func__", None) not in _FORWARD:
+    no gradient is wanted, keep_states is off, there is no room, or the
+    problem's own forward() has to be asked for the whole rollout."""
+    if not (keep and every and p.keep_states) or nsteps <= 0 or getattr(p.forward, "__func__", None) not in _FORWARD:
         return 0
     s0, s1 = segments(nsteps, every)[-1]
     return s1 - s0 if _room(fields * (s1 - s0) * f0.numel() * f0.element_size(), p.ctx.device) else 0
@@ -78,7 +81,8 @@ class FrozenCavity:
     passes (BGK_FLAG_ADJOINT).  precision: "fp64", or "fp32" for FP32
     storage of f and of its adjoint (reductions stay FP64).  x: positions
     [d][N] of the frozen cloud (a torch tensor or numpy array; default the
-    workload's initial cloud), e.g. where a moving-cloud run left it."""
+    workload's initial cloud), e.g. where a moving-cloud run left it.
+    keep_states: see the top of the file (False: least memory)."""
 
     def __init__(self, cav, device="cuda", seed=None, stream=None, precision="fp64", x=None,
                  keep_states=True, **overrides):
@@ -162,19 +166,13 @@ class _Rollout(torch.autograd.Function):
     @staticmethod
     def forward(actx, f0, lid, problem, nsteps, every, ke_weight, keep=False):
         p, c = problem, problem.ctx
-        n = _tail(p, f0, nsteps, every, keep, 2 if p.keep_states else 1)
+        n = _tail(p, f0, nsteps, every, keep, 2)
         (f, rho, U, T), saved = p.forward(f0, lid, nsteps - n, every)
         last = None
         if n:
             saved[nsteps - n] = (f, U.clone())
-            if p.keep_states:
-                last = _kept_segment(p, f, saved[nsteps - n][1], n)
-                _, f, rho, U, _ = last[-1][2]
-            else:
-                last = _states(lambda f, fn, st: B.bgk_step(c, f, fn, p.x, st[0], rho, T), f, (U,),
-                               n)
-                f, U = torch.empty_like(f), last[-1][1].clone()
-                B.bgk_step(c, last[-1][0], f, p.x, U, rho, T)
+            last = _kept_segment(p, f, saved[nsteps - n][1], n)
+            _, f, rho, U, _ = last[-1][2]
         J = B.bgk_objective(c, f, rho, U, ke_weight, want_grad=False)
         actx.problem, actx.nsteps, actx.every, actx.ke = problem, nsteps, every, ke_weight
         actx.final = (f, rho, U)
@@ -195,7 +193,7 @@ class _Rollout(torch.autograd.Function):
         dlid = torch.zeros(1, dtype=torch.float64, device=c.device)
         first = True  # only the last step's rho, T feed the objective
         # the kept segment goes with its use (a second backward recomputes it)
-        last, actx.last = actx.last, None
+        last, actx.last = actx.last if p.keep_states else None, None
         for s0, s1 in reversed(segments(actx.nsteps, actx.every)):
             fs, Us = actx.saved[s0]
             if p.keep_states:
@@ -207,11 +205,9 @@ class _Rollout(torch.autograd.Function):
                                             lam_rho if first else None, None, lam_f, lam_U, dlid)
                     first = False
                 continue
-            if last is None:
-                rho_t, T_t = torch.empty_like(rho), torch.empty_like(rho)
-                last = _states(lambda f, fn, st: B.bgk_step(c, f, fn, p.x, st[0], rho_t, T_t),
-                               fs, (Us,), s1 - s0)
-            states, last = last, None
+            rho_t, T_t = torch.empty_like(rho), torch.empty_like(rho)
+            states = _states(lambda f, fn, st: B.bgk_step(c, f, fn, p.x, st[0], rho_t, T_t),
+                             fs, (Us,), s1 - s0)
             while states:
                 fn, Un = states.pop()
                 B.bgk_adjoint_step(c, fn, Un, p.x, lam_f, lam_U, lam_rho if first else None,
@@ -242,13 +238,16 @@ def rollout_objective(problem: FrozenCavity, f0: torch.Tensor, lid: torch.Tensor
 class MovingCavity:
     """A cavity on one GPU whose cloud moves with the gas (S8), set up for
     forward and reverse passes through the positions (BGK_FLAG_ADJOINT,
-    move = 1).  precision: "fp64" or "fp32" storage of f and its adjoint."""
+    move = 1).  precision: "fp64" or "fp32" storage of f and its adjoint.
+    keep_states: False holds no states from a forward pass to its backward
+    but those at the segment starts."""
 
     def __init__(self, cav, device="cuda", seed=None, stream=None, precision="fp64",
-                 **overrides):
+                 keep_states=True, **overrides):
         if precision not in ("fp64", "fp32"):
             raise ValueError("the reverse mode runs in fp64 or fp32 storage")
         self.cav = cav
+        self.keep_states = bool(keep_states)
         overrides = dict(overrides)
         overrides.update(move=1, flags=overrides.get("flags", 0) | B.BGK_FLAG_ADJOINT)
         self.cfg = B.config_from(cav, precision, **overrides)

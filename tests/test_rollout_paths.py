@@ -140,3 +140,19 @@ def test_a_problem_with_its_own_forward_is_asked_for_the_whole_rollout(kernels, 
     got = torch.autograd.grad(rollout(p, f0, lid, 3, 2), [f0, lid])
     assert seen == [(3, 2)]
     assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("kind", ["frozen", "moving"])
+@pytest.mark.parametrize("nsteps,every", [(3, 3), (5, 2)])
+def test_without_keep_states_only_segment_starts_wait_for_the_backward(kernels, kind, nsteps,
+                                                                       every):
+    p = problem(kind)
+    f0, lid = inputs()
+    want = torch.autograd.grad(rollout(p, f0, lid, nsteps, every), [f0, lid])
+    p.keep_states = False
+    kernels.calls.clear()
+    J = rollout(p, f0, lid, nsteps, every)
+    assert J.grad_fn.last is None and sorted(J.grad_fn.saved) == list(range(0, nsteps, every))
+    assert len(kernels.calls) == nsteps
+    got = torch.autograd.grad(J, [f0, lid])
+    assert all(torch.equal(a, b) for a, b in zip(got, want))

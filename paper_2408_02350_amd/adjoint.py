@@ -43,9 +43,13 @@ def _room(nbytes: int, device) -> bool:
     """Whether the last segment's arrays may stay allocated between a forward
     pass and its backward: at most a quarter of the free memory, so that
     graphs kept side by side take ever less and the backward pass, which
-    needs as much again for a segment before it, has room."""
-    return (not torch.cuda.is_current_stream_capturing()
-            and 4 * nbytes <= torch.cuda.mem_get_info(device)[0])
+    needs as much again for a segment before it, has room.  Free is what the
+    driver and the caching allocator together can hand out: the blocks of an
+    earlier pass wait in the latter."""
+    if torch.cuda.is_current_stream_capturing():
+        return False
+    cached = torch.cuda.memory_reserved(device) - torch.cuda.memory_allocated(device)
+    return 4 * nbytes <= torch.cuda.mem_get_info(device)[0] + cached
 
 
 def _march(step, f, nsteps, every, *state):

@@ -156,3 +156,32 @@ def test_without_keep_states_only_segment_starts_wait_for_the_backward(kernels, 
     assert len(kernels.calls) == nsteps
     got = torch.autograd.grad(J, [f0, lid])
     assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("free,reserved,allocated,room", [
+    (400, 0, 0, True), (399, 0, 0, False), (0, 900, 500, True), (0, 900, 501, False),
+    (300, 200, 100, True),
+])
+def test_room_counts_what_the_allocator_holds_unused(monkeypatch, free, reserved, allocated, room):
+    cuda = {"is_current_stream_capturing": lambda: False, "mem_get_info": lambda d: (free, 1000),
+            "memory_reserved": lambda d: reserved, "memory_allocated": lambda d: allocated}
+    for name, fn in cuda.items():
+        monkeypatch.setattr(torch.cuda, name, fn)
+    assert A._room(100, "cuda:0") is room
+
+
+@pytest.mark.parametrize("kind", ["kept", "moving"])
+@pytest.mark.parametrize("nsteps,every", [(3, 3), (5, 2)])
+def test_the_kept_segment_is_not_run_again_but_by_a_second_backward(kernels, kind, nsteps, every):
+    p = problem(kind)
+    f0, lid = inputs()
+    J = rollout(p, f0, lid, nsteps, every)
+    assert J.grad_fn.last is not None and len(kernels.calls) == nsteps
+    ran = []
+    for _ in range(2):
+        kernels.calls.clear()
+        torch.autograd.grad(J, [f0, lid], retain_graph=True)
+        ran.append(len(kernels.calls))
+    # a segment of n steps: n run with all that the reverse reads, or its n states in n - 1
+    run = [b - a - (kind == "moving") for a, b in A.segments(nsteps, every)]
+    assert ran == [sum(run[:-1]), sum(run)]

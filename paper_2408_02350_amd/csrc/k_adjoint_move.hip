@@ -329,10 +329,11 @@ __global__ __launch_bounds__(kOpsWaves * 64) void k_adjm_ops(const MoveAdjArgs a
 // One block per wall particle (wall-list order): for every stencil entry
 // the dot product of the adjoint reaching the interpolated half with the
 // interior row f^{n+1}_j it interpolates.  Entries are taken eight at a time,
-// so the wall row is read once per eight and eight row loads are in flight;
-// 16-byte pieces whose adjoint is zero (the emitted half) skip f^{n+1}.  Bound
-// by the L2: 3458 wall particles x 14^3 280 -> 118 us, 396 x 24^2
-// 16 -> 14, against one entry at a time over the whole row.
+// so the wall row is read once per eight and eight row loads are in flight.
+// The emitted half is read too, so that 0 x inf and 0 x NaN of an overflowed
+// f^{n+1} stay in the sum (leaving out 16-byte pieces of zero adjoint: 117
+// against 132 us at 3458 wall particles x 14^3).  Bound by the L2: 3458 x 14^3
+// 280 -> 132 us, 396 x 24^2 16 -> 14, against one entry at a time.
 template <int NC, typename Real, int R>
 __global__ __launch_bounds__(kThreads) void k_adjm_wallrow(const MoveAdjArgs a, const Real* larr,
                                                            const Real* f1) {
@@ -357,10 +358,6 @@ __global__ __launch_bounds__(kThreads) void k_adjm_wallrow(const MoveAdjArgs a, 
       for (int c = 0; c < NC; ++c) {
         Real l[R];
         load_rs<Real, R>(lk + c * NVs + static_cast<size_t>(g) * R, l);
-        bool any = false;
-#pragma unroll
-        for (int r = 0; r < R; ++r) any = any || l[r] != Real(0);
-        if (!any) continue;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
           if (e >= en) break;  // (block-uniform)

@@ -137,7 +137,9 @@ __device__ __forceinline__ double halve_pair(double a, double b) {
 // of every edge, the wave reduces the 4 D*D sums (two halving steps by lane
 // swaps, then the 16-lane rows by DPP moves), and the waves' parts are
 // added in wave order once per kOpsB edges.  i's own rows stay in registers
-// when one group per lane covers the grid.  Bound by FP64 VALU issue and the
+// when one group per lane covers the grid.  (A difference of two sums: an
+// infinite sdf gives NaN at every k.  An infinite f^n makes f~ and with it the
+// whole row's adjoint NaN before this kernel reads it.)  Bound by FP64 VALU issue and the
 // latency of its row loads at 2-3 waves per SIMD: 6.04 -> 1.95 ms at 25^3 x
 // 14^3 and 0.58 -> 0.16 ms at 100^2 x 24^2 against one block sum of D*D
 // values, with two barriers, per edge and one velocity per thread.
@@ -165,6 +167,9 @@ __global__ __launch_bounds__(kOpsWaves * 64) void k_adjm_ops(const MoveAdjArgs a
   double Ui[D];
 #pragma unroll
   for (int q = 0; q < D; ++q) Ui[q] = U[static_cast<size_t>(q) * a.N + i];
+  bool nan = false;
+#pragma unroll
+  for (int q = 0; q < D; ++q) nan = nan || Ui[q] != Ui[q];
 
   // group g: byte offset of its first velocity, w = v - U there
   double w0[D];
@@ -319,8 +324,9 @@ __global__ __launch_bounds__(kOpsWaves * 64) void k_adjm_ops(const MoveAdjArgs a
       const int e = x / DD, k = x - e * DD;
       double s = 0.0;
       for (int w = 0; w < nw; ++w) s = s + part[e][w][k];
-      // (the self edge has zero operators and takes no part)
-      lam_a[(row + b0) * DD + x] = a.nidx[row + b0 + e] == i ? 0.0 : -a.dt * s;
+      // (the self edge has zero operators and takes no part; nor does any edge
+      // under a NaN velocity, where no projection is negative)
+      lam_a[(row + b0) * DD + x] = nan || a.nidx[row + b0 + e] == i ? 0.0 : -a.dt * s;
     }
   }
 }

@@ -102,6 +102,52 @@ __device__ __forceinline__ void block_sum(double (&v)[K], double* sh) {
   __syncthreads();
 }
 
+// A lane's value moved within its 16-lane DPP row.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const unsigned long long u = static_cast<unsigned long long>(__double_as_longlong(v));
+  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(u & 0xffffffffu), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(u >> 32), CTRL, 0xF, 0xF, true);
+  return __longlong_as_double(static_cast<long long>(
+      (static_cast<unsigned long long>(static_cast<unsigned>(hi)) << 32) | static_cast<unsigned>(lo)));
+}
+
+// Sum of v over the 16 lanes of a DPP row, left in every lane of the row.
+// Each step adds a lane's value to that of its partner (xor 1, xor 2, the
+// mirrored quad, the mirrored half); IEEE addition is commutative, so every
+// lane of the row ends with the same bits.
+__device__ __forceinline__ double row16_sum(double v) {
+  v = v + dpp_f64<0xB1>(v);   // quad_perm [1,0,3,2]
+  v = v + dpp_f64<0x4E>(v);   // quad_perm [2,3,0,1]
+  v = v + dpp_f64<0x141>(v);  // row_half_mirror
+  v = v + dpp_f64<0x140>(v);  // row_mirror
+  return v;
+}
+
+// A sum with the rounding errors of its additions (two-sum, Knuth 1969) beside
+// it, and its row sum.
+struct Sum2 {
+  double hi = 0.0, lo = 0.0;
+  __device__ __forceinline__ void add(double x) {
+    const double t = hi + x, b = t - hi;
+    lo = lo + ((hi - (t - b)) + (x - b));
+    hi = t;
+  }
+};
+template <int CTRL>
+__device__ __forceinline__ void sum2_step(Sum2& v) {
+  const double h = dpp_f64<CTRL>(v.hi), l = dpp_f64<CTRL>(v.lo);
+  v.add(h);
+  v.lo = v.lo + l;
+}
+__device__ __forceinline__ double row16_sum(Sum2 v) {
+  sum2_step<0xB1>(v);
+  sum2_step<0x4E>(v);
+  sum2_step<0x141>(v);
+  sum2_step<0x140>(v);
+  return v.hi + v.lo;
+}
+
 // R elements of a row at a stride of zsb bytes (the lane's byte offset of the
 // first in lane_off; the element offsets in scalar registers).  Lanes with
 // consecutive offsets read one contiguous piece per element.

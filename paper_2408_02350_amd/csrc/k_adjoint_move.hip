@@ -85,46 +85,6 @@ __global__ void k_adjm_move_prep(const MoveAdjArgs a, int D) {
 }
 
 // ------------------------------------------------------------ S4: lam_a
-// Sum of v over the 16 lanes of a DPP row, left in every lane of the row
-// (xor 1, xor 2, half mirror, mirror).
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const unsigned long long u = static_cast<unsigned long long>(__double_as_longlong(v));
-  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(u & 0xffffffffu), CTRL, 0xF, 0xF, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(u >> 32), CTRL, 0xF, 0xF, true);
-  return __longlong_as_double(static_cast<long long>(
-      (static_cast<unsigned long long>(static_cast<unsigned>(hi)) << 32) | static_cast<unsigned>(lo)));
-}
-__device__ __forceinline__ double row16_sum(double v) {
-  v = v + dpp_f64<0xB1>(v);
-  v = v + dpp_f64<0x4E>(v);
-  v = v + dpp_f64<0x141>(v);
-  v = v + dpp_f64<0x140>(v);
-  return v;
-}
-// A sum with the rounding errors of its additions (two-sum, Knuth 1969) beside
-// it, and its row sum.
-struct Sum2 {
-  double hi = 0.0, lo = 0.0;
-  __device__ __forceinline__ void add(double x) {
-    const double t = hi + x, b = t - hi;
-    lo = lo + ((hi - (t - b)) + (x - b));
-    hi = t;
-  }
-};
-template <int CTRL>
-__device__ __forceinline__ void sum2_step(Sum2& v) {
-  const double h = dpp_f64<CTRL>(v.hi), l = dpp_f64<CTRL>(v.lo);
-  v.add(h);
-  v.lo = v.lo + l;
-}
-__device__ __forceinline__ double row16_sum(Sum2 v) {
-  sum2_step<0xB1>(v);
-  sum2_step<0x4E>(v);
-  sum2_step<0x141>(v);
-  sum2_step<0x140>(v);
-  return v.hi + v.lo;
-}
 // One halving step of a reduce-scatter of two values a, b: with the upper
 // lanes of a and the lower lanes of b exchanged, a + b holds a's pair sums in
 // the lower lanes and b's in the upper ones.  W = 32: halves of the wave,

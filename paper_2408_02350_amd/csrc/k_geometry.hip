@@ -460,29 +460,6 @@ struct WlsArgs {
   int32_t* err;
 };
 
-// Sum of v over the 16 lanes of a DPP row, left in every lane of the row.
-// Each step adds a lane's value to that of its partner (xor 1, xor 2, the
-// mirrored quad, the mirrored half); IEEE addition is commutative, so every
-// lane of the row ends with the same bits.
-template <int CTRL>
-__device__ __forceinline__ double row_dpp(double v) {
-  const unsigned long long u = static_cast<unsigned long long>(__double_as_longlong(v));
-  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(u & 0xffffffffu), CTRL, 0xF,
-                                             0xF, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(u >> 32), CTRL, 0xF, 0xF, true);
-  return __longlong_as_double(static_cast<long long>(
-      (static_cast<unsigned long long>(static_cast<unsigned>(hi)) << 32) |
-      static_cast<unsigned>(lo)));
-}
-
-__device__ __forceinline__ double row_sum16(double v) {
-  v = v + row_dpp<0xB1>(v);   // quad_perm [1,0,3,2]
-  v = v + row_dpp<0x4E>(v);   // quad_perm [2,3,0,1]
-  v = v + row_dpp<0x141>(v);  // row_half_mirror
-  v = v + row_dpp<0x140>(v);  // row_mirror
-  return v;
-}
-
 // Basis functions of a fit of configured degree DEG.
 template <int D, int DEG>
 constexpr int wls_b() { return DEG == 0 ? D : Basis<D, DEG == 0 ? 1 : DEG>::B; }
@@ -581,7 +558,7 @@ __device__ __forceinline__ void wls_rows(const WlsArgs& a, int pidx, bool valid,
     }
   }
 #pragma unroll
-  for (int t = 0; t < NT; ++t) A[t] = row_sum16(A[t]);
+  for (int t = 0; t < NT; ++t) A[t] = row16_sum(A[t]);
   if (deg < DEG) {
 #pragma unroll
     for (int r = D + 1; r < B; ++r) A[tri(r, r)] = 1.0;

@@ -82,26 +82,6 @@ struct VelDigits {
   }
 };
 
-// Sum K doubles over a block of kThreads (= 4 waves of 64) in a fixed order;
-// every thread receives the totals.  sh must hold 4*K doubles.
-template <int K>
-__device__ __forceinline__ void block_sum(double (&v)[K], double* sh) {
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < K; ++k) sh[wid * K + k] = v[k];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < K; ++k) v[k] = ((sh[k] + sh[K + k]) + sh[2 * K + k]) + sh[3 * K + k];
-  __syncthreads();
-}
-
 // A lane's value moved within its 16-lane DPP row.
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
@@ -125,27 +105,76 @@ __device__ __forceinline__ double row16_sum(double v) {
 }
 
 // A sum with the rounding errors of its additions (two-sum, Knuth 1969) beside
-// it, and its row sum.
+// it.  The error of hi + h is exact, so add is commutative.
 struct Sum2 {
   double hi = 0.0, lo = 0.0;
-  __device__ __forceinline__ void add(double x) {
-    const double t = hi + x, b = t - hi;
-    lo = lo + ((hi - (t - b)) + (x - b));
+  __device__ __forceinline__ void add(double h, double l = 0.0) {
+    const double t = hi + h, b = t - hi;
+    lo = (lo + l) + ((hi - (t - b)) + (h - b));
     hi = t;
   }
+  // (an infinite sum has no error to add: lo is a NaN then)
+  __device__ __forceinline__ double value() const { return isfinite(hi) ? hi + lo : hi; }
 };
-template <int CTRL>
-__device__ __forceinline__ void sum2_step(Sum2& v) {
-  const double h = dpp_f64<CTRL>(v.hi), l = dpp_f64<CTRL>(v.lo);
-  v.add(h);
-  v.lo = v.lo + l;
+
+// Such a sum over a 16-lane row, left in every lane.
+__device__ __forceinline__ Sum2 row16_sum2(Sum2 v) {
+  v.add(dpp_f64<0xB1>(v.hi), dpp_f64<0xB1>(v.lo));
+  v.add(dpp_f64<0x4E>(v.hi), dpp_f64<0x4E>(v.lo));
+  v.add(dpp_f64<0x141>(v.hi), dpp_f64<0x141>(v.lo));
+  v.add(dpp_f64<0x140>(v.hi), dpp_f64<0x140>(v.lo));
+  return v;
 }
-__device__ __forceinline__ double row16_sum(Sum2 v) {
-  sum2_step<0xB1>(v);
-  sum2_step<0x4E>(v);
-  sum2_step<0x141>(v);
-  sum2_step<0x140>(v);
-  return v.hi + v.lo;
+
+// Sum K doubles over a block of kThreads (= 4 waves of 64) in a fixed order;
+// every thread receives the totals.  sh must hold 4*K doubles.
+template <int K>
+__device__ __forceinline__ void block_sum(double (&v)[K], double* sh) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) sh[wid * K + k] = v[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < K; ++k) v[k] = ((sh[k] + sh[K + k]) + sh[2 * K + k]) + sh[3 * K + k];
+  __syncthreads();
+}
+
+// The same with the rounding errors of all but the first two additions per
+// lane, since the partial sums of a sum that cancels are largest late; sh must
+// hold 8*K doubles.
+template <int K>
+__device__ __forceinline__ void block_sum2(double (&v)[K], double* sh) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    Sum2 s;
+    s.hi = v[k] + dpp_f64<0xB1>(v[k]);
+    s.hi = s.hi + dpp_f64<0x4E>(s.hi);
+    s.add(dpp_f64<0x141>(s.hi));
+    s.add(dpp_f64<0x140>(s.hi), dpp_f64<0x140>(s.lo));
+    s.add(__shfl_xor(s.hi, 16, 64), __shfl_xor(s.lo, 16, 64));
+    s.add(__shfl_xor(s.hi, 32, 64), __shfl_xor(s.lo, 32, 64));
+    if (lane == 0) {
+      sh[(wid * K + k) * 2] = s.hi;
+      sh[(wid * K + k) * 2 + 1] = s.lo;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    Sum2 s;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) s.add(sh[(w * K + k) * 2], sh[(w * K + k) * 2 + 1]);
+    v[k] = s.value();
+  }
+  __syncthreads();
 }
 
 // R elements of a row at a stride of zsb bytes (the lane's byte offset of the

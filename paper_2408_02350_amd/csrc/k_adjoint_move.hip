@@ -760,7 +760,7 @@ __global__ __launch_bounds__(64) void k_adjm_wallgeom(const MoveAdjArgs a) {
       for (int s = 0; s <= r; ++s) As[tri_m(r, s)].add(w * p[r] * p[s]);
   }
 #pragma unroll
-  for (int t = 0; t < NT; ++t) A[t] = row16_sum(As[t]);
+  for (int t = 0; t < NT; ++t) A[t] = row16_sum2(As[t]).value();
   const bool ok = m >= D + 2 && chol_m<B>(A, inv);
   double z[B], rhs[B], LZ[B], K[B];
 #pragma unroll
@@ -776,7 +776,7 @@ __global__ __launch_bounds__(64) void k_adjm_wallgeom(const MoveAdjArgs a) {
     }
   }
 #pragma unroll
-  for (int r = 0; r < B; ++r) LZ[r] = row16_sum(LZs[r]);
+  for (int r = 0; r < B; ++r) LZ[r] = row16_sum2(LZs[r]).value();
   chol_solve_m<B>(A, inv, LZ, K);
   double own[D];
 #pragma unroll

@@ -62,6 +62,14 @@ def kernel_source_hash():
     return h.hexdigest()
 
 
+def transport_kernel(dim, nv, precision):
+    """What forms S4-S6: the transport and the relaxation apart where a 3D
+    FP64 grid does not fit one block of 1024 lanes of 1, 2 or 4 velocities
+    (as plan_fused and launch_fused in csrc/k_fused.hip choose)."""
+    lanes = min(nv ** dim // r for r in (1, 2, 4) if nv % r == 0)
+    return "k_walk + k_collide" if dim == 3 and precision == "fp64" and lanes > 1024 else "k_fused"
+
+
 def measured_traffic(workload, precision):
     """HBM bytes per launch of the transport and relaxation from the committed counter
     summary (FETCH_SIZE and WRITE_SIZE scaled by a plain copy), or None when
@@ -484,10 +492,8 @@ def main():
     else:
         roof = {"bound": "hbm", "achieved": ach_gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": ach_gbs / PEAK_HBM_GBS}
-    # (3D FP64 grids of several tiles take the transport and the relaxation apart)
-    walk = cav.dim == 3 and args.precision == "fp64" and cav.n_velocities > 6144
     roof.update({"traffic": measured_traffic(cav.name, args.precision),
-                 "kernel": "k_walk + k_collide" if walk else "k_fused",
+                 "kernel": transport_kernel(cav.dim, cav.nv, args.precision),
                  "kernel_ms": k_ms, "kernel_updates_per_s": updates / (k_ms * 1e-3),
                  "algorithmic_bytes": bytes_, "algorithmic_ops": ops, "ops_per_update": k,
                  "hbm_frac": ach_gbs / PEAK_HBM_GBS, "alu_frac": ach_tops / PEAK_VALU_TOPS,

@@ -447,7 +447,7 @@ __device__ __forceinline__ void edge_frame(const double* dl, double* n, double* 
 }
 
 struct WlsArgs {
-  int N, cap, Ni, deg_cfg;
+  int N, cap, Ni;
   double h, alpha;
   const double* x;
   const int32_t* plist;  // interior particles
@@ -695,7 +695,7 @@ static size_t wls_smem(int D, int cap) {
 
 hipError_t launch_wls(const Ctx& c, const double* x, const int32_t* cnt, const int32_t* idx,
                       double* grad, double* ops, float* ops32, int32_t* degree) {
-  WlsArgs a{c.N, c.cap, c.Ni, c.cfg.wls_degree, c.cfg.h, c.cfg.alpha, x, c.d.cperm, cnt, idx,
+  WlsArgs a{c.N, c.cap, c.Ni, c.cfg.h, c.cfg.alpha, x, c.d.cperm, cnt, idx,
             grad, ops, ops32, degree, c.d.err};
   if (c.Ni == 0) return hipSuccess;
   const size_t sm = wls_smem(c.D, c.cap);
@@ -1015,13 +1015,9 @@ static hipError_t launch_geom_t(const Ctx& c, GeomArgs a) {
   a.off_wls = up(a.off_rows + static_cast<size_t>(P) * c.cap * sizeof(int32_t));
   a.off_psm = up(a.off_wls + wls_smem(D, c.cap));
   const size_t patch = a.off_psm + static_cast<size_t>(4) * P * c.cap * sizeof(int32_t);
+  // (at most 61360 bytes, in 3D at the largest capacity of 255, and 1844 of
+  // its own: under the 64 KB that need no attribute)
   const size_t lds = std::max(patch, 4 * sizeof(ValueRowSm<D>));
-  if (lds > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_geom_small<D, P, DEG>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             static_cast<int>(lds));
-    if (e != hipSuccess) return e;
-  }
   const unsigned nb = c.npatch + blocks_for(2 * static_cast<int64_t>(c.Nw), 4);
   if (nb == 0) return hipSuccess;
   hipLaunchKernelGGL((k_geom_small<D, P, DEG>), dim3(nb), dim3(256), lds, c.stream, a);
@@ -1037,7 +1033,7 @@ bool geometry_small(const Ctx& c) { return c.N <= (c.D == 2 ? 7168 : 5120); }
 hipError_t launch_geometry_small(const Ctx& c, const double* x) {
   const Dev& d = c.d;
   GeomArgs a{nbr_args(c, x, d.ncnt, d.nidx),
-             WlsArgs{c.N, c.cap, c.Ni, c.cfg.wls_degree, c.cfg.h, c.cfg.alpha, x, d.cperm, d.ncnt,
+             WlsArgs{c.N, c.cap, c.Ni, c.cfg.h, c.cfg.alpha, x, d.cperm, d.ncnt,
                      d.nidx, nullptr, d.ops64, d.ops32, nullptr, d.err},
              WallArgs{cloud_view(c, x), d.wall_list, d.wcnt, d.widx, d.wc0, d.whb, d.err},
              c.Nw, c.npatch, c.ucap, d.ucount, d.uj, d.ue, 0, 0, 0};

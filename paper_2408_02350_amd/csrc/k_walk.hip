@@ -204,9 +204,8 @@ static hipError_t launch_walk_r(const Ctx& c, WalkArgs a) {
   return hipGetLastError();
 }
 
-bool walk_supported(const Ctx& c) {
-  return c.D == 3 && c.cfg.precision == BGK_FP64 && c.tp == kWalkP && c.cfg.nv >= 8;
-}
+// (such clouds have patches of kWalkP, and a grid of several tiles has nv >= 14)
+bool walk_supported(const Ctx& c) { return c.D == 3 && c.cfg.precision == BGK_FP64; }
 
 // R: of 5 (three waves per SIMD) and 6 to 8 (two), the least waves x (R + 1.6),
 // an edge's set-up being worth about 1.6 velocities, with 8% against the

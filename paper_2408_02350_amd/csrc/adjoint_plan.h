@@ -31,7 +31,7 @@ hipError_t launch_adjoint_step_kept(const Ctx& c, const void* f_n, const double*
 // R velocities per lane for the interior patches, stepping along z in 3D
 // and x in 2D.  FP32 storage: 4 when 4 divides nv, else 2, and in 3D 5 when 5
 // divides nv (the increments of a line start at its multiples of R, so another
-// R would round differently).  FP64: any R up to 4 in 2D and 7 in 3D, the last
+// R would round differently).  FP64: 2 to 4 in 2D and 2 or 4 to 7 in 3D, the last
 // group of a line overlapping where R does not divide nv, at the least
 // tiles * (R + 2): an edge costs about as much set-up as two velocities (2D
 // nv = 24: 3 223 us, 4 271, 2 278; 3D nv = 12: 6 1.17 ms, 4 1.41; nv = 18: 6

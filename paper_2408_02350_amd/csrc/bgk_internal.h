@@ -88,9 +88,9 @@ struct Adj {
   void* larr;         // [Nw][n_c][N_v] adjoint reaching the interpolated wall values
   double* lidpart;    // [max(Nw,1)]
   double* gpart;      // [tiles][d][N] per-tile parts of lam_U (reverse transport)
-  int32_t* ucount;    // [(N+1)/2]   unions of the reverse transport's 2-particle patches
-  int32_t* uj;        // [(N+1)/2][2*cap]
-  uint32_t* ue;       // [(N+1)/2][2*cap]
+  int32_t* ucount;    // [npa]        unions of the reverse transport's patches of P particles
+  int32_t* uj;        // [npa][P*cap] (npa = ceil(N/P), P of adj_plan: 2 in 2D, 1 in 3D)
+  uint32_t* ue;       // [npa][P*cap]
 };
 
 // Workspace of the reverse step with the moving cloud (BGK_FLAG_ADJOINT with

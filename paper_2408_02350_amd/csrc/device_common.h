@@ -147,34 +147,32 @@ __device__ __forceinline__ void block_sum(double (&v)[K], double* sh) {
 }
 
 // The same with the rounding errors of all but the first two additions per
-// lane, since the partial sums of a sum that cancels are largest late; sh must
-// hold 8*K doubles.
+// lane, since the partial sums of a sum that cancels are largest late: the
+// quads' sums meet in LDS, and wave k adds those of value k (relaxation of 10648
+// x 8^3 doubles 32 us; 46 with every wave adding every value, 38 with
+// block_sum).  sh must hold 65*K doubles.
 template <int K>
 __device__ __forceinline__ void block_sum2(double (&v)[K], double* sh) {
+  static_assert(K <= kThreads / 64, "a wave per sum");
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
   for (int k = 0; k < K; ++k) {
+    double s = v[k] + dpp_f64<0xB1>(v[k]);
+    s = s + dpp_f64<0x4E>(s);
+    if ((lane & 3) == 0) sh[k * 64 + wid * 16 + (lane >> 2)] = s;
+  }
+  __syncthreads();
+  if (wid < K) {
     Sum2 s;
-    s.hi = v[k] + dpp_f64<0xB1>(v[k]);
-    s.hi = s.hi + dpp_f64<0x4E>(s.hi);
-    s.add(dpp_f64<0x141>(s.hi));
-    s.add(dpp_f64<0x140>(s.hi), dpp_f64<0x140>(s.lo));
+    s.hi = sh[wid * 64 + lane];
+    s = row16_sum2(s);
     s.add(__shfl_xor(s.hi, 16, 64), __shfl_xor(s.lo, 16, 64));
     s.add(__shfl_xor(s.hi, 32, 64), __shfl_xor(s.lo, 32, 64));
-    if (lane == 0) {
-      sh[(wid * K + k) * 2] = s.hi;
-      sh[(wid * K + k) * 2 + 1] = s.lo;
-    }
+    if (lane == 0) sh[K * 64 + wid] = s.value();
   }
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-    Sum2 s;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) s.add(sh[(w * K + k) * 2], sh[(w * K + k) * 2 + 1]);
-    v[k] = s.value();
-  }
-  __syncthreads();
+  for (int k = 0; k < K; ++k) v[k] = sh[K * 64 + k];
 }
 
 // R elements of a row at a stride of zsb bytes (the lane's byte offset of the

@@ -1144,7 +1144,9 @@ static hipError_t launch_adj_patch(const Ctx& c, const AdjArgs<Real>& a, const A
 }
 
 // S5-S6 adjoint: 16-byte row pieces (R = 2 doubles, or 4 floats when 4
-// divides nv), and 32 registers of the adjoint of f' kept per thread.
+// divides nv), and of each of the two rows 8 or 16 values per thread in
+// registers, or 32 floats, the fewest that hold the row (longer rows: 16
+// doubles, 32 floats).
 template <int D, int NC, typename Real>
 static void launch_adj_collide(const Ctx& c, const AdjArgs<Real>& a, dim3 t, size_t lds) {
   auto go = [&](auto r, auto keep) {

@@ -1,11 +1,12 @@
 // S5-S8 and the moment / Maxwellian helpers.
 //
 // One block of 256 threads owns one particle's row of f (all velocities,
-// all components).  Each thread always handles the same velocities
-// q = tid, tid + 256, ..., so every value it reads back in a later pass was
-// written by itself (no cross-thread hazards inside a block).  Moment sums
-// are FP64 in every precision mode, reduced in a fixed order (wavefront
-// butterflies, then the four waves in order), so results are deterministic.
+// all components).  Each thread always handles the same groups of R
+// consecutive velocities, tid, tid + 256, ... (one velocity in the Maxwellian),
+// so every value it reads back in a later pass was written by itself (no
+// cross-thread hazards inside a block).  Moment sums are FP64 in every
+// precision mode, reduced in a fixed order (lane moves within the wave, then
+// the waves in order), so results are deterministic.
 #include <algorithm>
 
 #include "device_common.h"
@@ -96,9 +97,7 @@ struct RowGroups {
 // U of a mixture of two Maxwellians, 11 grids of 8^2 to 64^2 and 8^3 to 24^3,
 // lies 1.9e-16 (relative, geometric mean) from 80-bit sums, 3.0e-16 with plain
 // ones (2.4e-16 with one velocity per thread at a time); rho 1.24e-16 and
-// 1.40e-16.  In lane moves within rows of 16 they take about what six plain
-// steps over the wave do (moments of 110592 x 8000 doubles 1.39 ms against
-// 1.30, floats 1.09 against 1.24).
+// 1.40e-16.
 template <int D, int NC, typename Real, int R, int KEEP>
 __device__ __forceinline__ void row_moments(const RowGroups<D, NC, Real, R, KEEP>& rg,
                                             const double* vt, double omega, double* sh,
@@ -177,10 +176,10 @@ struct CollideArgs {
 // S5-S6: moments of ft, tau at the new state, f = (tau ft + dt M)/(tau + dt).
 // One block per particle.  Bound by HBM: one read and one write of the row;
 // 110592 particles x 8000 doubles 3.87 -> 2.40 ms (5.2 TB/s), floats
-// 2.99 -> 1.69, against three reads of one value per thread.
+// 2.99 -> 1.60, against three reads of one value per thread.
 template <int D, int NC, typename Real, int R, int KEEP>
 __global__ __launch_bounds__(kThreads) void k_collide(const CollideArgs a) {
-  __shared__ double sh[8 * (D + 1)];
+  __shared__ double sh[65 * (D + 1)];
   extern __shared__ double vt[];  // nodes, then per-axis Maxwellian factors
   const int i = a.plist[xcd_logical_block(blockIdx.x, gridDim.x)];
   const int nv = a.nv;
@@ -719,12 +718,12 @@ hipError_t launch_wall_bc(const Ctx& c, void* f, double* rho, double* U, double*
 
 // ------------------------------------------------------------ moments, M
 // Bound by HBM: one read of the row.  110592 particles x 8000 floats
-// 1.79 -> 1.09 ms, doubles 2.20 -> 1.39, against two reads of one value per thread.
+// 1.79 -> 0.98 ms, doubles 2.20 -> 1.22, against two reads of one value per thread.
 template <int D, int NC, typename Real, int R, int KEEP>
 __global__ __launch_bounds__(kThreads) void k_moments(int N, int NV, int nv, double vmax,
                                                        double omega, const void* fv, double* rho,
                                                        double* U, double* T) {
-  __shared__ double sh[8 * (D + 1)];
+  __shared__ double sh[65 * (D + 1)];
   extern __shared__ double vt[];
   const int i = blockIdx.x;
   const size_t NVs = NV, cs = static_cast<size_t>(N) * NVs;
@@ -781,7 +780,7 @@ __global__ __launch_bounds__(kThreads) void k_state_terms(int N, int NV, int nv,
                                                            const double* __restrict__ U,
                                                            const double* __restrict__ T,
                                                            double* __restrict__ part) {
-  __shared__ double sh[8 * (D + 1)];
+  __shared__ double sh[65 * (D + 1)];
   __shared__ double smin[4];
   extern __shared__ double vt[];
   const int i = blockIdx.x;

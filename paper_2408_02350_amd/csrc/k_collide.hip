@@ -147,14 +147,22 @@ __device__ __forceinline__ void row_moments(const RowGroups<D, NC, Real, R, KEEP
 // beyond the row's need cost resident blocks, and with them latency where a
 // cloud has few particles (relaxation of 1331 x 14^3 floats: 32 values 26.5
 // us, 16 19.2; moments of 10000 x 24^2 x 2 doubles: 32 values 39, 8 35).
+// Floats in pieces of 8 bytes keep 8 values whatever the row: 32 take 182
+// registers in 16 groups, and a second read of the row from the L2 costs less
+// than the waves (relaxation of 10648 particles, us at 8 and 32 values, and with
+// one velocity per thread and three reads: 18^3 134, 212, 183; 22^3 250, 381,
+// 342; 26^3 401, 671, 549; 16 values lie between).
 template <typename Real, int NC, typename F>
 static void with_row_groups(int nv, int NV, F&& f) {
   auto keep = [&](auto r) {
     constexpr int R = r();
     const int64_t row = static_cast<int64_t>(NC) * NV;
-    if (row <= 8 * kThreads) f(r, std::integral_constant<int, 8 / (R * NC)>{});
-    else if (row <= 16 * kThreads) f(r, std::integral_constant<int, 16 / (R * NC)>{});
-    else f(r, std::integral_constant<int, 32 / (R * NC)>{});
+    constexpr bool half = R * sizeof(Real) < 16;  // 8-byte pieces
+    if (half || row <= 8 * kThreads) return f(r, std::integral_constant<int, 8 / (R * NC)>{});
+    if constexpr (!half) {
+      if (row <= 16 * kThreads) f(r, std::integral_constant<int, 16 / (R * NC)>{});
+      else f(r, std::integral_constant<int, 32 / (R * NC)>{});
+    }
   };
   if constexpr (sizeof(Real) == 4)
     if (nv % 4 == 0) return keep(std::integral_constant<int, 4>{});

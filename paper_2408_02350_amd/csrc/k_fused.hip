@@ -505,13 +505,23 @@ __global__ __launch_bounds__(1024) void k_fused(const FusedArgs a) {
                 for (int w = 0; w < W; ++w) rv[i * W + w] = x[w];
               }
             }
+            // (all rows, then all a_k.U: read in another order, BF16 in 3D
+            // takes 1.4% longer)
+            Real av[DD], bk[D];
+#pragma unroll
+            for (int k = 0; k < D; ++k)
+#pragma unroll
+              for (int m = 0; m < D; ++m)
+                av[k * D + m] = (RZ0 && k == D - 1 && m == D - 1) ? Real(0) : rc(ia(k, m));
+#pragma unroll
+            for (int k = 0; k < D; ++k) bk[k] = rc(ib(k));
 #pragma unroll
             for (int k = 0; k < D; ++k) {
-              Real s1 = -rc(ib(k));
+              Real s1 = -bk[k];
 #pragma unroll
-              for (int m = 0; m < FA; ++m) s1 = fma_t(rc(ia(k, m)), v0[m], s1);
+              for (int m = 0; m < FA; ++m) s1 = fma_t(av[k * D + m], v0[m], s1);
               pre[k] = s1;
-              as[k] = rc(ia(k, FA));
+              as[k] = av[k * D + FA];
               p[k] = at(k, v0[FA]);
             }
           }

@@ -77,7 +77,8 @@ def _tail(p, f0, nsteps, every, keep, fields):
     backward, ``fields`` f-sized arrays each: the last segment, or none where
     no gradient is wanted, keep_states is off, there is no room, or the
     problem's own forward() has to be asked for the whole rollout."""
-    if not (keep and every and p.keep_states) or nsteps <= 0 or getattr(p.forward, "__func__", None) not in _FORWARD:
+    own = getattr(p.forward, "__func__", None) not in _FORWARD
+    if not keep or own or not p.keep_states or not every or nsteps <= 0:
         return 0
     s0, s1 = segments(nsteps, every)[-1]
     return s1 - s0 if _room(fields * (s1 - s0) * f0.numel() * f0.element_size(), p.ctx.device) else 0
@@ -248,6 +249,8 @@ class MovingCavity:
     move = 1).  precision: "fp64" or "fp32" storage of f and its adjoint.
     keep_states: False holds no states from a forward pass to its backward
     but those at the segment starts."""
+
+    keep_states = True
 
     def __init__(self, cav, device="cuda", seed=None, stream=None, precision="fp64",
                  keep_states=True, **overrides):

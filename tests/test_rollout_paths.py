@@ -75,7 +75,9 @@ def problem(kind):
     base = A.MovingCavity if kind == "moving" else A.FrozenCavity
     p = object.__new__(base)
     p.ctx = types.SimpleNamespace(device="cpu", moves=kind == "moving")
-    p.N, p.keep_states = 1, kind != "states"
+    p.N = 1
+    if kind != "moving":  # (a moving cavity without the attribute keeps states)
+        p.keep_states = kind != "states"
     p.x = p.x0 = torch.full((1, 1), 0.5, dtype=F64)
     return p
 

@@ -15,8 +15,8 @@ on the device.  With ``keep_states=False`` the segment keeps only its
 states and every ``bgk_adjoint_step`` recomputes its step (one f-sized
 array per step, twice the forward work; the same gradients bit for bit).
 The last segment, which the backward pass walks first, is run by the forward
-pass in the same way where its arrays take at most a quarter of the free
-device memory, and is not recomputed (3 steps of 48^3 x 20^3 FP32 in one
+pass in the same way where its arrays, with those of other such graphs,
+take at most a quarter of the free device memory, and is not recomputed (3 steps of 48^3 x 20^3 FP32 in one
 segment 151 -> 118 ms, 20 of 100^2 x 24^2 FP64 in two 11.1 -> 10.1).  They
 stay allocated until the backward pass or the end of the graph; a program
 that needs the memory in between turns this off with ``keep_states=False``,
@@ -24,6 +24,9 @@ under which nothing but the segment starts is held between the passes.
 All arithmetic runs in libbgk; torch only holds the buffers.
 """
 from __future__ import annotations
+
+import threading
+import weakref
 
 import torch
 
@@ -39,20 +42,44 @@ def segments(nsteps: int, every: int):
     return [(s0, min(s0 + every, nsteps)) for s0 in range(0, nsteps, every)]
 
 
+class _Kept(list):
+    """The last segment's steps, from a forward pass to its backward."""
+
+    __hash__ = object.__hash__  # (told apart by identity, for the set below)
+    __eq__ = object.__eq__
+
+    def __init__(self, steps, device, nbytes):
+        super().__init__(steps)
+        self.device, self.step_bytes = device, nbytes // len(steps)
+        with _live_lock:
+            _live.add(self)
+
+
+_live, _live_lock = weakref.WeakSet(), threading.Lock()
+
+
+def _held(device) -> int:
+    """Bytes that the segments of all live graphs hold."""
+    with _live_lock:
+        return sum(len(k) * k.step_bytes for k in _live if k.device == device)
+
+
 def _room(nbytes: int, device) -> bool:
     """Whether the last segment's arrays may stay allocated between a forward
-    pass and its backward: at most a quarter of the free memory, so that
-    graphs kept side by side take ever less and the backward pass, which
-    needs as much again for a segment before it, has room.  Free is what the
-    driver and the caching allocator together can hand out: the blocks of an
-    earlier pass wait in the latter."""
+    pass and its backward: together with those of other graphs at most a
+    quarter of the memory free without them, so that graphs kept side by side
+    stay within it and the backward pass, which needs as much again for a
+    segment before it, has room.  Free is what the driver and the caching
+    allocator together can hand out: the blocks of an earlier pass wait in
+    the latter."""
     if torch.cuda.is_current_stream_capturing():
         return False
-    free = torch.cuda.mem_get_info(device)[0]
-    if 4 * nbytes <= free:  # (the allocator's counters take 77 us to read)
+    held = _held(device)
+    free = torch.cuda.mem_get_info(device)[0] + held
+    if 4 * (nbytes + held) <= free:  # (the allocator's counters take 77 us to read)
         return True
     cached = torch.cuda.memory_reserved(device) - torch.cuda.memory_allocated(device)
-    return 4 * nbytes <= free + cached
+    return 4 * (nbytes + held) <= free + cached
 
 
 def _march(step, f, nsteps, every, *state):
@@ -81,7 +108,8 @@ def _tail(p, f0, nsteps, every, keep, fields):
     if not keep or own or not p.keep_states or not every or nsteps <= 0:
         return 0
     s0, s1 = segments(nsteps, every)[-1]
-    return s1 - s0 if _room(fields * (s1 - s0) * f0.numel() * f0.element_size(), p.ctx.device) else 0
+    return s1 - s0 if _room((s1 - s0) * fields * f0.numel() * f0.element_size(),
+                            p.ctx.device) else 0
 
 
 class FrozenCavity:
@@ -179,7 +207,8 @@ class _Rollout(torch.autograd.Function):
         last = None
         if n:
             saved[nsteps - n] = (f, U.clone())
-            last = _kept_segment(p, f, saved[nsteps - n][1], n)
+            last = _Kept(_kept_segment(p, f, saved[nsteps - n][1], n), c.device,
+                         2 * n * f.numel() * f.element_size())
             _, f, rho, U, _ = last[-1][2]
         J = B.bgk_objective(c, f, rho, U, ke_weight, want_grad=False)
         actx.problem, actx.nsteps, actx.every, actx.ke = problem, nsteps, every, ke_weight
@@ -308,8 +337,8 @@ class _RolloutMove(torch.autograd.Function):
         last = None
         if n:
             saved[nsteps - n] = (f, U.clone(), x.clone())
-            last = _states(lambda f, fn, st: B.bgk_step(c, f, fn, st[1], st[0], rho, T), f, (U, x),
-                           n)
+            last = _Kept(_states(lambda f, fn, st: B.bgk_step(c, f, fn, st[1], st[0], rho, T),
+                                 f, (U, x), n), c.device, n * f.numel() * f.element_size())
             fa, U, x = last[-1][0], last[-1][1].clone(), last[-1][2].clone()
             f = torch.empty_like(fa)
             B.bgk_step(c, fa, f, x, U, rho, T)

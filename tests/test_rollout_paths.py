@@ -187,3 +187,28 @@ def test_the_kept_segment_is_not_run_again_but_by_a_second_backward(kernels, kin
     # a segment of n steps: n run with all that the reverse reads, or its n states in n - 1
     run = [b - a - (kind == "moving") for a, b in A.segments(nsteps, every)]
     assert ran == [sum(run[:-1]), sum(run)]
+
+
+@pytest.mark.parametrize("kind", ["kept", "moving"])
+def test_graphs_side_by_side_keep_a_quarter_together(monkeypatch, kernels, kind):
+    monkeypatch.undo()
+    monkeypatch.setattr(A, "B", kernels)
+    p = problem(kind)
+    f0, lid = inputs()
+    segment = 3 * (2 if kind == "kept" else 1) * f0.numel() * f0.element_size()
+    total = 9 * segment  # room for two segments, not for a third
+
+    def kept():
+        return sum(len(k) * k.step_bytes for k in A._live)
+
+    cuda = {"is_current_stream_capturing": lambda: False, "memory_reserved": lambda d: 0,
+            "mem_get_info": lambda d: (total - kept(), total), "memory_allocated": lambda d: 0}
+    for name, fn in cuda.items():
+        monkeypatch.setattr(torch.cuda, name, fn)
+    Js = [rollout(p, f0, lid, 3, 3) for _ in range(4)]
+    assert [J.grad_fn.last is not None for J in Js] == [True, True, False, False]
+    assert kept() == 2 * segment
+    torch.autograd.grad(Js[0], lid)  # used up
+    Js[1] = None                     # dropped
+    assert kept() == 0
+    assert rollout(p, f0, lid, 3, 3).grad_fn.last is not None

@@ -8,6 +8,7 @@
 // precision mode, reduced in a fixed order (lane moves within the wave, then
 // the waves in order), so results are deterministic.
 #include <algorithm>
+#include <type_traits>
 
 #include "device_common.h"
 
@@ -316,8 +317,13 @@ struct WallBcArgs {
   const int32_t* wuj;
   const uint32_t* wue;
   int wucap;
-  // the position update of the interior particles (S8) by the blocks after
-  // the nwb wall blocks: it needs their U, which the walls leave alone
+};
+
+// With the position update of the interior particles (S8) by the blocks after
+// the nwb wall blocks: it needs their U, which the walls leave alone.  (A launch
+// without it keeps the shorter arguments: 33.0 against 32.6 us at 488 wall
+// particles x 16^3 floats.)
+struct WallMoveArgs : WallBcArgs {
   int nwb;
   MoveArgs mv;
 };
@@ -404,7 +410,8 @@ __device__ __forceinline__ void store_vec(Real* __restrict__ p, const Real (&x)[
 // launch without them is an instance of its own, 36.3 against 36.9 us at
 // 488 wall particles x 16^3 doubles)
 template <int D, int NC, typename Real, int R, int P, bool MOVE>
-__global__ __launch_bounds__(kThreads) void k_wall_bc(const WallBcArgs a) {
+__global__ __launch_bounds__(kThreads) void k_wall_bc(
+    const std::conditional_t<MOVE, WallMoveArgs, WallBcArgs> a) {
   // v_k [nv], exp(-(v_k - Uw_a)^2 / (2 T_w)) [D][nv]; wall patches then
   // hold the union's weights [wucap][P] and rows [wucap]
   extern __shared__ double wtab[];
@@ -423,7 +430,9 @@ __global__ __launch_bounds__(kThreads) void k_wall_bc(const WallBcArgs a) {
       return;
     }
   }
-  const int k = xcd_logical_block(blockIdx.x, MOVE ? a.nwb : gridDim.x);  // neighbouring walls share an L2
+  int nwb = gridDim.x;
+  if constexpr (MOVE) nwb = a.nwb;
+  const int k = xcd_logical_block(blockIdx.x, nwb);  // neighbouring walls share an L2
   const int nw = blockDim.x >> 6;
   int kt[P], bt[P];  // wall-list slot and particle of each patch entry (-1: empty)
 #pragma unroll
@@ -674,38 +683,34 @@ __global__ __launch_bounds__(kThreads) void k_wall_bc(const WallBcArgs a) {
 }
 
 template <int D, int NC, typename Real, int R>
-static void wall_bc_r(const Ctx& c, WallBcArgs a, dim3 t, size_t lds) {
-  if constexpr (D == 3) {  // wall patches are formed in 3D only
-    if (c.npw > 0) {
-      const size_t ul = static_cast<size_t>(c.wucap) * (kWallPatch * sizeof(double) + sizeof(int32_t));
-      a.nwb = c.npw;
-      if (a.mv.blocks)
-        hipLaunchKernelGGL((k_wall_bc<D, NC, Real, R, kWallPatch, true>),
-                           dim3(a.nwb + a.mv.blocks), t, lds + ul, c.stream, a);
-      else
-        hipLaunchKernelGGL((k_wall_bc<D, NC, Real, R, kWallPatch, false>), dim3(a.nwb), t,
-                           lds + ul, c.stream, a);
-      return;
+static void wall_bc_r(const Ctx& c, const WallBcArgs& a, const MoveArgs& mv, dim3 t, size_t lds) {
+  auto go = [&](auto p, int nwb, size_t l) {
+    if (mv.blocks) {
+      WallMoveArgs m{a, nwb, mv};
+      hipLaunchKernelGGL((k_wall_bc<D, NC, Real, R, p(), true>), dim3(nwb + mv.blocks), t, l,
+                         c.stream, m);
+    } else {
+      hipLaunchKernelGGL((k_wall_bc<D, NC, Real, R, p(), false>), dim3(nwb), t, l, c.stream, a);
     }
+  };
+  if constexpr (D == 3) {  // wall patches are formed in 3D only
+    if (c.npw > 0)
+      return go(std::integral_constant<int, kWallPatch>{}, c.npw,
+                lds + static_cast<size_t>(c.wucap) * (kWallPatch * sizeof(double) + sizeof(int32_t)));
   }
-  a.nwb = c.Nw;
-  if (a.mv.blocks)
-    hipLaunchKernelGGL((k_wall_bc<D, NC, Real, R, 1, true>), dim3(a.nwb + a.mv.blocks), t, lds,
-                       c.stream, a);
-  else
-    hipLaunchKernelGGL((k_wall_bc<D, NC, Real, R, 1, false>), dim3(a.nwb), t, lds, c.stream, a);
+  go(std::integral_constant<int, 1>{}, c.Nw, lds);
 }
 
 template <int D, int NC, typename Real>
-static void wall_bc_t(const Ctx& c, const WallBcArgs& a) {
+static void wall_bc_t(const Ctx& c, const WallBcArgs& a, const MoveArgs& mv) {
   const int hv = c.cfg.nv / 2;  // nv is even
   const int R = hv % 4 == 0 ? 4 : (hv % 2 == 0 ? 2 : 1);
   const int groups = c.NV / (2 * R);
   const dim3 t(std::min(kThreads, (groups + 63) / 64 * 64));
   const size_t lds = static_cast<size_t>(D + 1) * c.cfg.nv * sizeof(double);
-  if (R == 4) wall_bc_r<D, NC, Real, 4>(c, a, t, lds);
-  else if (R == 2) wall_bc_r<D, NC, Real, 2>(c, a, t, lds);
-  else wall_bc_r<D, NC, Real, 1>(c, a, t, lds);
+  if (R == 4) wall_bc_r<D, NC, Real, 4>(c, a, mv, t, lds);
+  else if (R == 2) wall_bc_r<D, NC, Real, 2>(c, a, mv, t, lds);
+  else wall_bc_r<D, NC, Real, 1>(c, a, mv, t, lds);
 }
 
 hipError_t launch_wall_bc(const Ctx& c, void* f, double* rho, double* U, double* T, double* x) {
@@ -713,13 +718,13 @@ hipError_t launch_wall_bc(const Ctx& c, void* f, double* rho, double* U, double*
   WallBcArgs a{c.N,          c.NV,      c.cfg.nv,      c.cap,  c.Nw,   c.D,    c.cfg.vmax,
                omega_of(c.cfg), c.lid,  c.cfg.wall_T,  c.d.wall_list, c.d.wall_id, c.d.wcnt,
                c.d.widx,     c.d.wc0,   f,             rho,    U,      T,      c.d.err,
-               c.d.wpl,      c.d.wucount, c.d.wuj,     c.d.wue, c.wucap, 0,
-               x ? move_of(c, x, U) : MoveArgs{}};
+               c.d.wpl,      c.d.wucount, c.d.wuj,     c.d.wue, c.wucap};
+  const MoveArgs mv = x ? move_of(c, x, U) : MoveArgs{};
   const bool f64 = c.cfg.precision == BGK_FP64;
   if (c.D == 2) {
-    if (f64) wall_bc_t<2, 2, double>(c, a); else wall_bc_t<2, 2, float>(c, a);
+    if (f64) wall_bc_t<2, 2, double>(c, a, mv); else wall_bc_t<2, 2, float>(c, a, mv);
   } else {
-    if (f64) wall_bc_t<3, 1, double>(c, a); else wall_bc_t<3, 1, float>(c, a);
+    if (f64) wall_bc_t<3, 1, double>(c, a, mv); else wall_bc_t<3, 1, float>(c, a, mv);
   }
   return hipGetLastError();
 }
